@@ -25,6 +25,7 @@ PRECISION = {"fp64": pond.FP64, "fp32": pond.FP32_STORE, "fp32_fp64math": pond.F
 # the Dieterici fluid with the critical density and temperature of the van der Waals fluid
 DIETERICI = dict(a=2.0 * W.T_CR / W.RHO_CR, b=0.5 / W.RHO_CR, R=1.0, T_cr=W.T_CR)
 U_CH = math.sqrt(W.P_CR / W.RHO_CR)
+SIDES = (64, 128, 256, 512, 256, 128, 512, 64)  # the jobs of a batch, in order
 
 
 def _case(name, flow, n, steps, precision="fp64", path="lattice", n_pass=2, **kw):
@@ -129,7 +130,7 @@ def _problem(case, seed, member=0):
     dim = case["dim"]
     n = (case["nx"], case["ny"], case["nz"])[:dim]
     if case["path"] == "batch":
-        side = (64, 128, 256, 512)[member % 4 if member < 4 else int(rng.integers(0, 4))]
+        side = SIDES[member]
         n = (side, side)
     shape = n[::-1]
     bc, inflow = ((0, 0),) * dim, ()
@@ -156,20 +157,20 @@ def _problem(case, seed, member=0):
         post = np.broadcast_to(x < x_shock, shape)
         rho = np.where(post, sh["rho1"], rho)
         T = np.where(post, sh["T1"], 0.95 * W.T_CR)
-        u = np.stack([np.where(post, sh["u1"], 0.0), np.zeros(shape)])
+        u = np.stack([np.where(post, sh["u1"], 0.0), 0.1 * U_CH * _modes(rng, shape)])
     elif case["flow"] == "dieterici":
         D = DIETERICI
         prm = W.base_params(omega=1.5, kappa=W.KAPPA_DROPLET, dt=0.2, eos=1, a=D["a"], b=D["b"], R=D["R"])
         rho = rng.uniform(2.0, 3.0) * (1.0 + 0.05 * _modes(rng, shape))
         T = rng.uniform(1.25, 1.35) * D["T_cr"] * (1.0 + 0.01 * _modes(rng, shape))
         u = np.stack([rng.uniform(-0.05, 0.05) + 0.02 * _modes(rng, shape) for _ in range(dim)])
-    else:  # droplets in their vapour, near rest
+    else:  # droplets in their vapour, in a slow flow
         prm = W.base_params(omega=1.5, kappa=W.KAPPA_DROPLET, dt=W.DT_DROPLET)
         tr = round(0.005 * int(rng.integers(180, 190)), 3)  # 0.900 .. 0.945 T_cr
         rv, rl = W.coexistence(tr)
         rho = _droplets(rng, shape, rv, rl, 1 if case["path"] != "batch" else int(rng.integers(1, 5)))
         T = tr * W.T_CR * (1.0 + 1e-3 * _modes(rng, shape))
-        u = np.stack([1e-2 * U_CH * _modes(rng, shape) for _ in range(dim)])
+        u = np.stack([0.2 * U_CH * _modes(rng, shape) for _ in range(dim)])
     prm = dict(prm, n_pass=case["n_pass"])
     return dict(dim=dim, n=n, shape=shape, bc=bc, inflow=inflow, prm=prm, rho=np.ascontiguousarray(rho),
                 u=np.ascontiguousarray(u), T=np.array(np.broadcast_to(T, shape)))
@@ -253,8 +254,7 @@ def work(case):
     nodes = case["nx"] * case["ny"] * case["nz"]
     steps = case["steps"]
     if case["path"] == "batch":
-        sides = [(64, 128, 256, 512)[m] if m < 4 else 256 for m in range(case["members"])]
-        nodes, steps = sum(s * s for s in sides), 2 * steps
+        nodes, steps = sum(s * s for s in SIDES[:case["members"]]), 2 * steps
     planes = 2 * Q if case["path"] == "noalloc" or D == 3 else {1: 6, 2: 18}[D]
     state = planes * (4 if fp32 else 8)
     full = sum(3 * 12 * 3 ** a * 12 ** (D - 1 - a) for a in range(D))  # FMA per set
