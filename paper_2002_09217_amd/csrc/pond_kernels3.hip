@@ -6,8 +6,9 @@
 // halo:
 //   k3_stream         one workgroup per x-y tile of one z plane; every predictor-corrector
 //                     pass stages the five donor planes z-2 .. z+2 through LDS, one z
-//                     power of one plane at a time, and accumulates for each the x-y
-//                     contraction of the D2Q9 kernel followed by the z contraction;
+//                     power of one plane at a time; the last pass accumulates for each the
+//                     x-y contraction of the D2Q9 kernel followed by the z contraction, the
+//                     passes before it only the sums that fix the next gauge;
 //   k3_korteweg, k3_thermo, k3_collide
 //                     Korteweg stress, force and thermodynamics, heat-flux correction and
 //                     the collisions of f and g (separate waves), 27-point stencils; the
@@ -295,6 +296,87 @@ __device__ __forceinline__ void xy_window(const LdsT *sbase, const LdsT (&wx)[3]
     }
 }
 
+// sum of a value over the two lanes of a receiver (lanes 2 i and 2 i + 1), the same bits
+// in both: a data-parallel move of the pair, no LDS round trip
+__device__ __forceinline__ double pair_sum(double v)
+{
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), 0xB1, 0xF, 0xF, true); // quad_perm 1,0,3,2
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), 0xB1, 0xF, 0xF, true);
+    return v + __hiloint2double(hi, lo);
+}
+
+// ---------------------------------------------------------------------------
+// A pass whose populations only fix the next gauge needs their sums rho, J = sum f c
+// (c the direction, so that the momentum is U rho + s J) and 2 rho E = sum g, not the
+// populations.  The sums separate: with the x weights folded over the directions,
+//   a0_m[c] = sum_k A_km wx_k[c],  a1_m[c] = sum_k (k - 1) A_km wx_k[c],
+// b0, b1 and g0, g1 likewise in y and z,
+//   rho = sum M g0 b0 a0, J_x = sum M g0 b0 a1, J_y = sum M g0 b1 a0, J_z = sum M g1 b0 a0
+// over the moments and the 5 x 5 x 5 window: 49 FMA per row of fifteen values of f and
+// of g, against 2 x 57 for the populations.  With two passes this took k3_stream from
+// 53.6 to 43.7 ms (FP64) and from 32.1 to 26.1 ms (FP32) at 256^3: fewer FMA, half the LDS
+// reads a pass (the pairs are read 16 bytes a lane, at twice the rate of 8), and the last
+// pass, now outside the pass loop, spills 68 bytes a lane instead of 272 (FP64 184, 396).
+//
+// row_sums adds one row (y index n, window row r) of a staged plane: each lane of a
+// receiver takes half the rows of both sets, so a window value pair (f, g) is one wide
+// LDS read and the lanes share the work evenly.
+// ---------------------------------------------------------------------------
+template <typename LdsT> struct SumRow; // staged layout of the sums passes
+template <> struct SumRow<double> {
+    // field (m, n) of both sets: (f, g) pairs, field by field
+    static __device__ __forceinline__ void load(const double *lds, int ln, int n, int node, int c, double f[3], double g[3])
+    {
+        const double2 *p = (const double2 *)lds + (n * ln + node);
+#pragma unroll
+        for (int m = 0; m < 3; ++m) {
+            const double2 v = p[3 * m * ln + c];
+            f[m] = v.x;
+            g[m] = v.y;
+        }
+    }
+    static __device__ __forceinline__ void store(double *lds, int ln, int n, int node, const double f[3], const double g[3])
+    {
+#pragma unroll
+        for (int m = 0; m < 3; ++m) ((double2 *)lds)[(3 * m + n) * ln + node] = double2{f[m], g[m]};
+    }
+};
+template <> struct SumRow<float> {
+    // (f_0, g_0, f_1, g_1) and (f_2, g_2) of each n: 16 and 8 bytes a read
+    static __device__ __forceinline__ void load(const float *lds, int ln, int n, int node, int c, float f[3], float g[3])
+    {
+        const float4 v = ((const float4 *)lds + (n * ln + node))[c];
+        const float2 w = ((const float2 *)(lds + 12 * ln) + (n * ln + node))[c];
+        f[0] = v.x, g[0] = v.y, f[1] = v.z, g[1] = v.w, f[2] = w.x, g[2] = w.y;
+    }
+    static __device__ __forceinline__ void store(float *lds, int ln, int n, int node, const float f[3], const float g[3])
+    {
+        ((float4 *)lds)[n * ln + node] = float4{f[0], g[0], f[1], g[1]};
+        ((float2 *)(lds + 12 * ln))[n * ln + node] = float2{f[2], g[2]};
+    }
+};
+template <typename LdsT>
+__device__ __forceinline__ void row_sums(const LdsT *lds, int ln, int n, int node, const LdsT (&a0)[3][5],
+                                         const LdsT (&a1)[3][5], LdsT b0, LdsT b1, LdsT (&Y)[4])
+{
+    LdsT x0 = (LdsT)0, x1 = (LdsT)0, xg = (LdsT)0;
+#pragma unroll
+    for (int c = 0; c < 5; ++c) {
+        LdsT f[3], g[3];
+        SumRow<LdsT>::load(lds, ln, n, node, c, f, g);
+#pragma unroll
+        for (int m = 0; m < 3; ++m) {
+            x0 += a0[m][c] * f[m];
+            x1 += a1[m][c] * f[m];
+            xg += a0[m][c] * g[m];
+        }
+    }
+    Y[0] += b0 * x0;
+    Y[1] += b0 * x1;
+    Y[2] += b1 * x0;
+    Y[3] += b0 * xg;
+}
+
 // ---------------------------------------------------------------------------
 // streaming passes: x-y tile of TX x TY receivers of one z plane, two lanes per
 // receiver (set f / g), the 5 x 5 x 5 window staged plane by plane.
@@ -324,7 +406,8 @@ __global__ void __launch_bounds__(2 * TX *TY, sizeof(LdsT) == 4 ? 3 : 2) k3_stre
     // C_mo wz_m[sz] of its rounds, the FP64 window the nine C_mo and fifteen wz_m[sz] whose
     // product each round forms (23 and 25 KB of LDS)
     constexpr int NR = TX * TY;
-    constexpr int kCz = kDev ? 45 : 24;
+    // (a sums pass keeps the fifteen g0 and fifteen g1 instead)
+    constexpr int kCz = kDev ? 45 : 30;
     __shared__ AccT s_cz[kCz * NR];
     __shared__ int s_wfast[NT / 64]; // per wave: its lanes allow the zero-tap-free window
     __shared__ int abort_block;
@@ -374,7 +457,142 @@ __global__ void __launch_bounds__(2 * TX *TY, sizeof(LdsT) == 4 ? 3 : 2) k3_stre
     double acc[27];
     double sU[3] = {U[0], U[1], U[2]}, sS = 1.0, rho = 0.0;
     int err = 0;
-    for (int pass = 0; pass < P.n_pass; ++pass) {
+    if (tid == 0) {
+        abort_block = err_before;
+        // one step more has started without an earlier failure
+        if (blockIdx.x == 0 && err_before == 0) atomicAdd(&flags[kFlagSteps], 1);
+    }
+    __syncthreads();
+    if (abort_block != 0) return;
+
+    // moments of the streamed populations (eq. 2) in the gauge (U, s) -> EoS closure -> the
+    // next gauge
+    auto close_pass = [&](double s, double r, const double (&j)[3], double G2) {
+        rho = r;
+        const double i_rho = 1.0 / rho; // one reciprocal for every quotient by rho
+        const double E = 0.5 * G2 * i_rho;
+        double uh2 = 0.0, un[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            un[a] = j[a] * i_rho;
+            const double uh = un[a] + 0.5 * Fp[a] * dt * i_rho;
+            uh2 += uh * uh;
+        }
+        const double e = E - 0.5 * uh2;
+        const double T = eos_T_of_e<GEN>(P, rho, e);
+        const double p = eos_p<GEN>(P, rho, T);
+        if (inside) err |= eos_bad<GEN>(P, rho, p);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            sU[a] = U[a];
+            U[a] = un[a];
+        }
+        sS = s;
+        th = p * i_rho * kInvTL;
+    };
+
+    // --- the passes before the last: sums only ------------------------------------
+#pragma unroll 1
+    for (int pass = 0; pass + 1 < P.n_pass; ++pass) {
+        const double s = sqrt(th);
+        const int h = myset; // lane 0 takes n = 0 and the low rows of n = 1, lane 1 mirrored
+        LdsT a0[3][5], a1[3][5], b0[8], b1[8];
+        int werr;
+        {
+            double w[3][5], C[3][3];
+            werr = window_weights<double>(U[0], s, dt, w);
+            lagrange_coeffs(U[0], s, C);
+#pragma unroll
+            for (int m = 0; m < 3; ++m)
+#pragma unroll
+                for (int c = 0; c < 5; ++c) {
+                    const double lo = C[0][m] * w[0][c], hi = C[2][m] * w[2][c];
+                    a0[m][c] = (LdsT)(lo + C[1][m] * w[1][c] + hi);
+                    a1[m][c] = (LdsT)(hi - lo);
+                }
+            werr |= window_weights<double>(U[1], s, dt, w);
+            lagrange_coeffs(U[1], s, C);
+            // rows 0..4 (lane 1: 4..0) of n = 0 (2), then rows 0..2 (4..2) of n = 1, whose
+            // middle row both lanes take with half its weight
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int r = j < 5 ? j : j - 5;
+                double q[3];
+#pragma unroll
+                for (int l = 0; l < 3; ++l)
+                    q[l] = (j < 5 ? (h ? C[l][2] : C[l][0]) : C[l][1]) * (h ? w[l][4 - r] : w[l][r]);
+                const double half = j == 7 ? 0.5 : 1.0;
+                b0[j] = (LdsT)(half * (q[0] + q[1] + q[2]));
+                b1[j] = (LdsT)(half * (q[2] - q[0]));
+            }
+            werr |= window_weights<double>(U[2], s, dt, w);
+            lagrange_coeffs(U[2], s, C);
+            if (inside) err |= werr; // lanes past the lattice edge only pad the tile
+            __syncthreads();         // ends the reads of the previous pass's z coefficients
+            // z coefficients of the rounds: lane 0 writes g0, lane 1 g1
+#pragma unroll
+            for (int o = 0; o < 3; ++o)
+#pragma unroll
+                for (int j = 0; j < 5; ++j) {
+                    const double lo = C[0][o] * w[0][j], hi = C[2][o] * w[2][j];
+                    s_cz[(2 * (5 * o + j) + h) * NR + rcv] = (AccT)(h ? hi - lo : lo + C[1][o] * w[1][j] + hi);
+                }
+        }
+        // row walk of this lane: n = 0 upwards or n = 2 downwards, then its rows of n = 1
+        const int nodeA = wbase + (h ? 4 * LX : 0), nA = h ? 2 : 0, dr = h ? -LX : LX;
+        double S[5] = {0.0, 0.0, 0.0, 0.0, 0.0}; // rho, J_x, J_y, J_z, 2 rho E (FP32: deviations)
+#pragma unroll 1
+        for (int szo = 0; szo < 15; ++szo) {
+            const int so = szo / 5, sz = szo - 5 * so;
+            __syncthreads();
+            if (stager) {
+                const unsigned off = (ndxy + plane * (unsigned)box.wrap(z + sz - 2, box.nz)) * (unsigned)sizeof(LdsT);
+                LdsT v[2][9];
+#pragma unroll
+                for (int i = 0; i < 9; ++i)
+#pragma unroll
+                    for (int set = 0; set < 2; ++set)
+                        v[set][i] = *(const POND_GLOBAL LdsT *)((const POND_GLOBAL char *)(dmom + (size_t)(27 * set + 3 * i + so) * N) + off);
+#pragma unroll
+                for (int n = 0; n < 3; ++n) {
+                    LdsT f[3], g[3];
+#pragma unroll
+                    for (int m = 0; m < 3; ++m) {
+                        f[m] = v[0][3 * m + n] - (kDev ? ref[9 * m + 3 * n + so] : (LdsT)0);
+                        g[m] = v[1][3 * m + n] - (kDev ? ref[27 + 9 * m + 3 * n + so] : (LdsT)0);
+                    }
+                    SumRow<LdsT>::store(lds, LN, n, tid, f, g);
+                }
+            }
+            __syncthreads();
+            LdsT Y[4] = {(LdsT)0, (LdsT)0, (LdsT)0, (LdsT)0};
+#pragma unroll
+            for (int j = 0; j < 5; ++j) row_sums<LdsT>(lds, LN, nA, nodeA + j * dr, a0, a1, b0[j], b1[j], Y);
+#pragma unroll
+            for (int j = 0; j < 3; ++j) row_sums<LdsT>(lds, LN, 1, nodeA + j * dr, a0, a1, b0[5 + j], b1[5 + j], Y);
+            const double g0 = (double)s_cz[(2 * szo) * NR + rcv], g1 = (double)s_cz[(2 * szo + 1) * NR + rcv];
+            S[0] += g0 * (double)Y[0];
+            S[1] += g0 * (double)Y[1];
+            S[2] += g0 * (double)Y[2];
+            S[3] += g1 * (double)Y[0];
+            S[4] += g0 * (double)Y[3];
+        }
+#pragma unroll
+        for (int i = 0; i < 5; ++i) S[i] = pair_sum(S[i]);
+        double j[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            j[a] = U[a] * S[0] + s * S[1 + a];
+            // the reference moments' own sums: every axis's weights reproduce a constant, and
+            // the Lagrange bases the moments themselves
+            if (kDev) j[a] += (double)ref[a == 0 ? 9 : a == 1 ? 3 : 1];
+        }
+        if (kDev) close_pass(s, (double)ref[0] + S[0], j, (double)ref[27] + S[4]);
+        else close_pass(s, S[0], j, S[4]);
+    }
+
+    // --- the last pass: populations --------------------------------------------------
+    {
         const double s = sqrt(th);
         LdsT wx[3][5], wy[3][5];
         double wz[3][5]; // only its halo check is kept: the z taps go to LDS in the first round
@@ -434,7 +652,7 @@ __global__ void __launch_bounds__(2 * TX *TY, sizeof(LdsT) == 4 ? 3 : 2) k3_stre
             }
         }
 
-        auto rounds = [&](auto fast_tag) -> bool {
+        auto rounds = [&](auto fast_tag) {
             constexpr bool FAST = decltype(fast_tag)::value;
 #pragma unroll 1
             for (int szo = 0; szo < 15; ++szo) {
@@ -476,13 +694,7 @@ __global__ void __launch_bounds__(2 * TX *TY, sizeof(LdsT) == 4 ? 3 : 2) k3_stre
                         }
                     }
                 }
-                if (pass == 0 && szo == 0 && tid == 0) {
-                    abort_block = err_before;
-                    // one step more has started without an earlier failure
-                    if (blockIdx.x == 0 && err_before == 0) atomicAdd(&flags[kFlagSteps], 1);
-                }
                 __syncthreads();
-                if (abort_block != 0) return false;
 
                 const LdsT *sbase = &lds[wbase * 2 + myset];
                 AccT Y[3][3];
@@ -503,9 +715,11 @@ __global__ void __launch_bounds__(2 * TX *TY, sizeof(LdsT) == 4 ? 3 : 2) k3_stre
                         for (int l = 0; l < 3; ++l) av[9 * k + 3 * l + m] += cz * Y[k][l];
                 }
             }
-            return true;
         };
-        if (!(block_fast ? rounds(std::true_type{}) : rounds(std::false_type{}))) return;
+        if (block_fast)
+            rounds(std::true_type{});
+        else
+            rounds(std::false_type{});
         if (kDev) {
             // reference part: sum_mno A_km B_ln C_m'o R_mno in FP64 (the window weights of
             // each axis sum to one).  The inputs pass an empty asm so that the coefficients
@@ -541,7 +755,7 @@ __global__ void __launch_bounds__(2 * TX *TY, sizeof(LdsT) == 4 ? 3 : 2) k3_stre
 #pragma unroll
             for (int q = 0; q < 27; ++q) acc[q] = (double)av[q];
         }
-        // moments of the streamed populations (eq. 2) and the EoS closure
+        // each lane sums its own set; the partner lane supplies the other sums
         double s0 = 0.0, sx = 0.0, sy = 0.0, szm = 0.0;
 #pragma unroll
         for (int q = 0; q < 27; ++q) {
@@ -552,29 +766,8 @@ __global__ void __launch_bounds__(2 * TX *TY, sizeof(LdsT) == 4 ? 3 : 2) k3_stre
         }
         const double o0 = __shfl_xor(s0, 1, 64), ox = __shfl_xor(sx, 1, 64);
         const double oy = __shfl_xor(sy, 1, 64), oz = __shfl_xor(szm, 1, 64);
-        rho = myset == 0 ? s0 : o0;
         const double j[3] = {myset == 0 ? sx : ox, myset == 0 ? sy : oy, myset == 0 ? szm : oz};
-        const double G2 = myset == 0 ? o0 : s0;
-        const double i_rho = 1.0 / rho; // one reciprocal for every quotient by rho
-        const double E = 0.5 * G2 * i_rho;
-        double uh2 = 0.0, un[3];
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            un[a] = j[a] * i_rho;
-            const double uh = un[a] + 0.5 * Fp[a] * dt * i_rho;
-            uh2 += uh * uh;
-        }
-        const double e = E - 0.5 * uh2;
-        const double T = eos_T_of_e<GEN>(P, rho, e);
-        const double p = eos_p<GEN>(P, rho, T);
-        if (inside) err |= eos_bad<GEN>(P, rho, p);
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            sU[a] = U[a];
-            U[a] = un[a];
-        }
-        sS = s;
-        th = p * i_rho * kInvTL;
+        close_pass(s, myset == 0 ? s0 : o0, j, myset == 0 ? o0 : s0);
     }
 
     if (inside) {
