@@ -230,20 +230,11 @@ __device__ __forceinline__ void store_donor_moments(const SlotDesc &S, size_t N,
     for (int i = 0; i < 27; ++i) out[(size_t)i * N + node] = (MomT)m[i];
 }
 
-// x-y contraction of the nine fields (m, n, o) of one z power o over a staged donor
-// plane, into Y[k][l] += sum_n B_ln sum_r wy_l[r] sum_m A_km sum_c wx_k[c] M_mno[r][c].
-// Each axis's cubic stencil covers four of the five window columns; for the directions
-// c = -1 and +1 the unused column is the first (k = 0) or the last (k = 2) whenever the
-// gauge velocity lies in (-s, s].  FAST (chosen per wave when every lane's weights
-// there are zero) leaves those zero taps out; the two variants agree to round-off, and
-// the choice depends only on the lanes of a wave, which the tile shape fixes.
-template <bool FAST, typename T>
-__device__ __forceinline__ T taps3(int k, const T w[5], T v0, T v1, T v2, T v3, T v4)
-{
-    if (FAST && k == 0) return w[1] * v1 + w[2] * v2 + w[3] * v3 + w[4] * v4;
-    if (FAST && k == 2) return w[0] * v0 + w[1] * v1 + w[2] * v2 + w[3] * v3;
-    return w[0] * v0 + w[1] * v1 + w[2] * v2 + w[3] * v3 + w[4] * v4;
-}
+// Window columns are read this many ahead of their use.  Left alone, the compiler reads a
+// column just before its nine FMA and waits for it, and the two or three waves of a SIMD do
+// not cover that (the FP64 kernel then issued VALU work 48% of the time).  Two to four
+// columns measured the same, five spilled.
+constexpr int kColumnsAhead = 3;
 
 // weight of window column j (0..4) in the cubic stencil of departure velocity v: the
 // column weights of window_weights, one at a time (its halo check is not repeated)
@@ -262,34 +253,73 @@ __device__ __forceinline__ double window_tap(double v, double dt, int j)
     return 0.0;
 }
 
-// the LDS holds the nine fields (m, n) of one z power, field (m, n) at slot 3 m + n; each
-// row is x-contracted and added straight into Y with its y weights (no five-row buffer:
-// the FP64 window must fit two waves per SIMD)
-template <bool FAST, typename LdsT, typename AccT, int LN, int LX>
-__device__ __forceinline__ void xy_window(const LdsT *sbase, const LdsT (&wx)[3][5], const LdsT (&wy)[3][5],
-                                          const LdsT (&A)[3][3], const AccT (&B)[3][3], AccT (&Y)[3][3])
+// Staged layout of the last pass: the nine fields (m, n) of one z power of a plane, for the
+// lane of each set: (M_0n, M_1n) in one read and M_2n in another, the sets of a node side
+// by side, so that a wave's reads are contiguous.  16-byte LDS reads move 240 bytes a clock
+// and CU, 8-byte ones 125 (FP64 k3_stream 43.5 -> 42.5 ms against a read per field).
+template <typename T, int LN> struct PopRow {
+    using T2 = typename std::conditional<sizeof(T) == 4, float2, double2>::type;
+    const T2 *p01;
+    const T *p2;
+    __device__ __forceinline__ PopRow(const T *lds, int node, int set)
+        : p01((const T2 *)lds + 2 * node + set), p2(lds + 12 * LN + 2 * node + set)
+    {
+    }
+    __device__ __forceinline__ void load(int n, int off, T v[3]) const
+    {
+        const T2 a = p01[2 * (n * LN + off)];
+        v[0] = a.x, v[1] = a.y, v[2] = p2[2 * (n * LN + off)];
+    }
+    static __device__ __forceinline__ void store(T *lds, int n, int node, const T f[3], const T g[3])
+    {
+        T2 *q = (T2 *)lds + 2 * (n * LN + node);
+        q[0] = T2{f[0], f[1]};
+        q[1] = T2{g[0], g[1]};
+        *(T2 *)(lds + 12 * LN + 2 * (n * LN + node)) = T2{f[2], g[2]};
+    }
+};
+
+// x-y contraction of the nine fields (m, n, o) of one z power o over a staged donor
+// plane, into Y[k][l] += sum_n B_ln sum_r wy_l[r] sum_m A_km sum_c wx_k[c] M_mno[r][c].
+// Each axis's cubic stencil covers four of the five window columns; for the directions
+// c = -1 and +1 the unused column is the first (k = 0) or the last (k = 2) whenever the
+// gauge velocity lies in (-s, s].  FAST (chosen per workgroup when every lane's weights
+// there are zero) leaves those zero taps out; the two variants agree to round-off.
+//
+// The plane is walked column by column, 75 columns of three fields, and each finished row
+// is added straight into Y with its y weights (no five-row buffer: the FP64 window must
+// fit two waves per SIMD).  Folding A_km into the taps (39 FMA a row instead of 48) was
+// slower: its registers went to scratch (FP64 42.5 -> 62.7 ms, FP32 26.5 -> 27.2 ms).
+template <bool FAST, typename LdsT, int LN, int LX>
+__device__ __forceinline__ void xy_window(const PopRow<LdsT, LN> &rows, const LdsT (&wx)[3][5], const LdsT (&wy)[3][5],
+                                          const LdsT (&A)[3][3], const LdsT (&B)[3][3], LdsT (&Y)[3][3])
 {
+    LdsT ring[kColumnsAhead][3], T[3][3];
+    auto load = [&](int i) { rows.load(i / 25, (i / 5) % 5 * LX + i % 5, ring[i % kColumnsAhead]); };
 #pragma unroll
-    for (int n = 0; n < 3; ++n) {
+    for (int i = 0; i < kColumnsAhead; ++i) load(i);
 #pragma unroll
-        for (int r = 0; r < 5; ++r) {
-            LdsT Zr[3];
+    for (int i = 0; i < 75; ++i) {
+        const int n = i / 25, r = i / 5 % 5, c = i % 5;
 #pragma unroll
-            for (int m = 0; m < 3; ++m) {
-                const LdsT *row = sbase + ((3 * m + n) * LN + r * LX) * 2;
-                const LdsT v0 = row[0], v1 = row[2], v2 = row[4], v3 = row[6], v4 = row[8];
+        for (int m = 0; m < 3; ++m)
 #pragma unroll
-                for (int k = 0; k < 3; ++k) {
-                    const LdsT x = taps3<FAST>(k, wx[k], v0, v1, v2, v3, v4);
-                    Zr[k] = m == 0 ? A[k][m] * x : Zr[k] + A[k][m] * x;
-                }
+            for (int k = 0; k < 3; ++k) {
+                if (FAST && ((k == 0 && c == 0) || (k == 2 && c == 4))) continue; // zero taps
+                const bool first = FAST && k == 0 ? c == 1 : c == 0;
+                T[k][m] = first ? wx[k][c] * ring[i % kColumnsAhead][m] : T[k][m] + wx[k][c] * ring[i % kColumnsAhead][m];
             }
+        if (i + kColumnsAhead < 75) load(i + kColumnsAhead);
+        if (c == 4) {
+            LdsT Z[3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) Z[k] = A[k][0] * T[k][0] + A[k][1] * T[k][1] + A[k][2] * T[k][2];
 #pragma unroll
             for (int l = 0; l < 3; ++l) {
                 if (FAST && ((l == 0 && r == 0) || (l == 2 && r == 4))) continue; // zero taps
-                const AccT c = B[l][n] * (AccT)wy[l][r];
+                const LdsT q = B[l][n] * wy[l][r];
 #pragma unroll
-                for (int k = 0; k < 3; ++k) Y[k][l] += c * (AccT)Zr[k];
+                for (int k = 0; k < 3; ++k) Y[k][l] += q * Z[k];
             }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -318,63 +348,78 @@ __device__ __forceinline__ double pair_sum(double v)
 // reads a pass (the pairs are read 16 bytes a lane, at twice the rate of 8), and the last
 // pass, now outside the pass loop, spills 68 bytes a lane instead of 272 (FP64 184, 396).
 //
-// row_sums adds one row (y index n, window row r) of a staged plane: each lane of a
-// receiver takes half the rows of both sets, so a window value pair (f, g) is one wide
+// Each lane of a receiver takes half the rows (y index n, window row r) of both sets, so a window value pair (f, g) is one wide
 // LDS read and the lanes share the work evenly.
 // ---------------------------------------------------------------------------
-template <typename LdsT> struct SumRow; // staged layout of the sums passes
-template <> struct SumRow<double> {
+template <typename LdsT, int LN> struct SumRow; // staged layout of the sums passes
+template <int LN> struct SumRow<double, LN> {
     // field (m, n) of both sets: (f, g) pairs, field by field
-    static __device__ __forceinline__ void load(const double *lds, int ln, int n, int node, int c, double f[3], double g[3])
+    static __device__ __forceinline__ void load(const double *lds, int n, int node, int c, double f[3], double g[3])
     {
-        const double2 *p = (const double2 *)lds + (n * ln + node);
+        const double2 *p = (const double2 *)lds + (n * LN + node);
 #pragma unroll
         for (int m = 0; m < 3; ++m) {
-            const double2 v = p[3 * m * ln + c];
+            const double2 v = p[3 * m * LN + c];
             f[m] = v.x;
             g[m] = v.y;
         }
     }
-    static __device__ __forceinline__ void store(double *lds, int ln, int n, int node, const double f[3], const double g[3])
+    static __device__ __forceinline__ void store(double *lds, int n, int node, const double f[3], const double g[3])
     {
 #pragma unroll
-        for (int m = 0; m < 3; ++m) ((double2 *)lds)[(3 * m + n) * ln + node] = double2{f[m], g[m]};
+        for (int m = 0; m < 3; ++m) ((double2 *)lds)[(3 * m + n) * LN + node] = double2{f[m], g[m]};
     }
 };
-template <> struct SumRow<float> {
+template <int LN> struct SumRow<float, LN> {
     // (f_0, g_0, f_1, g_1) and (f_2, g_2) of each n: 16 and 8 bytes a read
-    static __device__ __forceinline__ void load(const float *lds, int ln, int n, int node, int c, float f[3], float g[3])
+    static __device__ __forceinline__ void load(const float *lds, int n, int node, int c, float f[3], float g[3])
     {
-        const float4 v = ((const float4 *)lds + (n * ln + node))[c];
-        const float2 w = ((const float2 *)(lds + 12 * ln) + (n * ln + node))[c];
+        const float4 v = ((const float4 *)lds + (n * LN + node))[c];
+        const float2 w = ((const float2 *)(lds + 12 * LN) + (n * LN + node))[c];
         f[0] = v.x, g[0] = v.y, f[1] = v.z, g[1] = v.w, f[2] = w.x, g[2] = w.y;
     }
-    static __device__ __forceinline__ void store(float *lds, int ln, int n, int node, const float f[3], const float g[3])
+    static __device__ __forceinline__ void store(float *lds, int n, int node, const float f[3], const float g[3])
     {
-        ((float4 *)lds)[n * ln + node] = float4{f[0], g[0], f[1], g[1]};
-        ((float2 *)(lds + 12 * ln))[n * ln + node] = float2{f[2], g[2]};
+        ((float4 *)lds)[n * LN + node] = float4{f[0], g[0], f[1], g[1]};
+        ((float2 *)(lds + 12 * LN))[n * LN + node] = float2{f[2], g[2]};
     }
 };
-template <typename LdsT>
-__device__ __forceinline__ void row_sums(const LdsT *lds, int ln, int n, int node, const LdsT (&a0)[3][5],
-                                         const LdsT (&a1)[3][5], LdsT b0, LdsT b1, LdsT (&Y)[4])
+// the rows of one lane over a staged plane: five rows of n = nA from node A, three of n = 1
+// from node B; the columns are read kColumnsAhead before their use, as in xy_window
+template <typename LdsT, int LN, int LX>
+__device__ __forceinline__ void plane_sums(const LdsT *lds, int nA, int A, int B, const LdsT (&a0)[3][5],
+                                           const LdsT (&a1)[3][5], const LdsT (&b0)[8], const LdsT (&b1)[8],
+                                           LdsT (&Y)[4])
 {
-    LdsT x0 = (LdsT)0, x1 = (LdsT)0, xg = (LdsT)0;
+    LdsT f[kColumnsAhead][3], g[kColumnsAhead][3], x0, x1, xg;
+    auto load = [&](int i) {
+        const int j = i / 5, s = i % kColumnsAhead;
+        if (j < 5)
+            SumRow<LdsT, LN>::load(lds, nA, A + j * LX, i % 5, f[s], g[s]);
+        else
+            SumRow<LdsT, LN>::load(lds, 1, B + (j - 5) * LX, i % 5, f[s], g[s]);
+    };
 #pragma unroll
-    for (int c = 0; c < 5; ++c) {
-        LdsT f[3], g[3];
-        SumRow<LdsT>::load(lds, ln, n, node, c, f, g);
+    for (int i = 0; i < kColumnsAhead; ++i) load(i);
+#pragma unroll
+    for (int i = 0; i < 40; ++i) {
+        const int j = i / 5, c = i % 5, s = i % kColumnsAhead;
 #pragma unroll
         for (int m = 0; m < 3; ++m) {
-            x0 += a0[m][c] * f[m];
-            x1 += a1[m][c] * f[m];
-            xg += a0[m][c] * g[m];
+            const bool first = c == 0 && m == 0;
+            x0 = first ? a0[m][c] * f[s][m] : x0 + a0[m][c] * f[s][m];
+            x1 = first ? a1[m][c] * f[s][m] : x1 + a1[m][c] * f[s][m];
+            xg = first ? a0[m][c] * g[s][m] : xg + a0[m][c] * g[s][m];
         }
+        if (i + kColumnsAhead < 40) load(i + kColumnsAhead);
+        if (c == 4) {
+            Y[0] += b0[j] * x0;
+            Y[1] += b0[j] * x1;
+            Y[2] += b1[j] * x0;
+            Y[3] += b0[j] * xg;
+        }
+        __builtin_amdgcn_sched_barrier(0);
     }
-    Y[0] += b0 * x0;
-    Y[1] += b0 * x1;
-    Y[2] += b1 * x0;
-    Y[3] += b0 * xg;
 }
 
 // ---------------------------------------------------------------------------
@@ -400,7 +445,11 @@ __global__ void __launch_bounds__(2 * TX *TY, sizeof(LdsT) == 4 ? 3 : 2) k3_stre
     // each (35 KB of LDS in FP64, 17 KB in FP32 instead of 104 and 52 KB for the whole
     // plane), so that two FP64 or three FP32 workgroups share a CU
     constexpr int FPS = 9; // fields per set and round
-    __shared__ __align__(16) LdsT lds[2 * FPS * LN];
+    // the sums passes pad their field stride to 4 mod 8 nodes: the two lanes of a receiver
+    // read n = 0 and n = 2, or rows 0 and 2 of n = 1, whose 16-byte pairs then lie 8 mod 16
+    // apart, so the sixteen lanes of a read (eight receivers) touch every bank once
+    constexpr int LNS = LN + (12 - LN % 8) % 8;
+    __shared__ __align__(16) LdsT lds[2 * FPS * LNS];
     __shared__ LdsT ref[kDev ? 54 : 1];
     // z coefficients of the pass, per receiver: the FP32 window keeps the 45 products
     // C_mo wz_m[sz] of its rounds, the FP64 window the nine C_mo and fifteen wz_m[sz] whose
@@ -427,16 +476,21 @@ __global__ void __launch_bounds__(2 * TX *TY, sizeof(LdsT) == 4 ? 3 : 2) k3_stre
     const int tiles_x = (box.nx + TX - 1) / TX;
     const int lb = xcd_tile((int)blockIdx.x, (int)gridDim.x);
     const int tile = lb / box.nz, z = lb - tile * box.nz;
-    const int bx0 = (tile % tiles_x) * TX, by0 = (tile / tiles_x) * TY;
+    // The tiles start two nodes into the row (the box is periodic), so that the rows of a
+    // tile's donor window, two nodes wider on each side, start at multiples of TX nodes: in
+    // boxes whose rows keep that alignment a 20-node row of doubles covers two 128-byte
+    // lines instead of three (256^3: 47.2 -> 45.4 ms FP64, 28.0 -> 27.4 FP32)
+    const int tx0 = (tile % tiles_x) * TX, by0 = (tile / tiles_x) * TY;
+    const int bx0 = tx0 + 2;
     const int lxr = (int)threadIdx.x >> 1, myset = (int)threadIdx.x & 1;
     const int rcv = lxr + TX * (int)threadIdx.y; // receiver index in the tile
-    const int gx = bx0 + lxr, gy = by0 + (int)threadIdx.y;
-    const bool inside = gx < box.nx && gy < box.ny;
-    const int node = min(gx, box.nx - 1) + box.nx * (min(gy, box.ny - 1) + box.ny * z);
+    const int gy = by0 + (int)threadIdx.y;
+    const bool inside = tx0 + lxr < box.nx && gy < box.ny;
+    const int node = box.wrap(bx0 + lxr, box.nx) + box.nx * (min(gy, box.ny - 1) + box.ny * z);
     const POND_GLOBAL double *side = (const POND_GLOBAL double *)S.side_src;
     const POND_GLOBAL LdsT *dmom = (const POND_GLOBAL LdsT *)S.dmom;
     if (kDev && tid < 54) {
-        const int cnode = min(bx0 + TX / 2, box.nx - 1) + box.nx * (min(by0 + TY / 2, box.ny - 1) + box.ny * z);
+        const int cnode = box.wrap(bx0 + TX / 2, box.nx) + box.nx * (min(by0 + TY / 2, box.ny - 1) + box.ny * z);
         ref[tid] = dmom[(size_t)tid * N + cnode]; // ordered before its readers by the first barrier
     }
     double U[3] = {side[kSideUx * N + node], side[kSideUy * N + node], side[kSideUz * N + node]};
@@ -452,7 +506,6 @@ __global__ void __launch_bounds__(2 * TX *TY, sizeof(LdsT) == 4 ? 3 : 2) k3_stre
     const unsigned ndxy = (unsigned)(box.wrap(bx0 - 2 + tid % LX, box.nx) +
                                      box.nx * box.wrap(by0 - 2 + tid / LX, box.ny));
     const unsigned plane = (unsigned)box.nx * (unsigned)box.ny;
-    using Pair = typename std::conditional<kDev, float2, double2>::type;
 
     double acc[27];
     double sU[3] = {U[0], U[1], U[2]}, sS = 1.0, rho = 0.0;
@@ -491,11 +544,39 @@ __global__ void __launch_bounds__(2 * TX *TY, sizeof(LdsT) == 4 ? 3 : 2) k3_stre
         th = p * i_rho * kInvTL;
     };
 
+    // the 18 fields of z power szo / 5 of this lane's window node in donor plane szo % 5, and
+    // their way into the LDS layout of a sums pass or of the last pass
+    auto fetch = [&](int szo, LdsT (&v)[2][9]) {
+        const int so = szo / 5, sz = szo - 5 * so;
+        const unsigned off = (ndxy + plane * (unsigned)box.wrap(z + sz - 2, box.nz)) * (unsigned)sizeof(LdsT);
+#pragma unroll
+        for (int i = 0; i < 9; ++i)
+#pragma unroll
+            for (int set = 0; set < 2; ++set)
+                v[set][i] = *(const POND_GLOBAL LdsT *)((const POND_GLOBAL char *)(dmom + (size_t)(27 * set + 3 * i + so) * N) + off);
+    };
+    auto stage = [&](int so, const LdsT (&v)[2][9], auto sums_tag) {
+        constexpr bool SUMS = decltype(sums_tag)::value;
+#pragma unroll
+        for (int n = 0; n < 3; ++n) {
+            LdsT f[3], g[3];
+#pragma unroll
+            for (int m = 0; m < 3; ++m) {
+                f[m] = v[0][3 * m + n] - (kDev ? ref[9 * m + 3 * n + so] : (LdsT)0);
+                g[m] = v[1][3 * m + n] - (kDev ? ref[27 + 9 * m + 3 * n + so] : (LdsT)0);
+            }
+            if constexpr (SUMS)
+                SumRow<LdsT, LNS>::store(lds, n, tid, f, g);
+            else
+                PopRow<LdsT, LN>::store(lds, n, tid, f, g);
+        }
+    };
+
     // --- the passes before the last: sums only ------------------------------------
 #pragma unroll 1
     for (int pass = 0; pass + 1 < P.n_pass; ++pass) {
         const double s = sqrt(th);
-        const int h = myset; // lane 0 takes n = 0 and the low rows of n = 1, lane 1 mirrored
+        const int h = myset; // lane 0 takes n = 0 and the low rows of n = 1, lane 1 the others
         LdsT a0[3][5], a1[3][5], b0[8], b1[8];
         int werr;
         {
@@ -512,16 +593,15 @@ __global__ void __launch_bounds__(2 * TX *TY, sizeof(LdsT) == 4 ? 3 : 2) k3_stre
                 }
             werr |= window_weights<double>(U[1], s, dt, w);
             lagrange_coeffs(U[1], s, C);
-            // rows 0..4 (lane 1: 4..0) of n = 0 (2), then rows 0..2 (4..2) of n = 1, whose
+            // the five rows of n = 0 (lane 1: n = 2), then rows 0..2 (2..4) of n = 1, whose
             // middle row both lanes take with half its weight
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                const int r = j < 5 ? j : j - 5;
                 double q[3];
 #pragma unroll
                 for (int l = 0; l < 3; ++l)
-                    q[l] = (j < 5 ? (h ? C[l][2] : C[l][0]) : C[l][1]) * (h ? w[l][4 - r] : w[l][r]);
-                const double half = j == 7 ? 0.5 : 1.0;
+                    q[l] = j < 5 ? (h ? C[l][2] : C[l][0]) * w[l][j] : C[l][1] * (h ? w[l][j - 3] : w[l][j - 5]);
+                const double half = j == 5 ? (h ? 0.5 : 1.0) : j == 7 ? (h ? 1.0 : 0.5) : 1.0;
                 b0[j] = (LdsT)(half * (q[0] + q[1] + q[2]));
                 b1[j] = (LdsT)(half * (q[2] - q[0]));
             }
@@ -538,38 +618,20 @@ __global__ void __launch_bounds__(2 * TX *TY, sizeof(LdsT) == 4 ? 3 : 2) k3_stre
                     s_cz[(2 * (5 * o + j) + h) * NR + rcv] = (AccT)(h ? hi - lo : lo + C[1][o] * w[1][j] + hi);
                 }
         }
-        // row walk of this lane: n = 0 upwards or n = 2 downwards, then its rows of n = 1
-        const int nodeA = wbase + (h ? 4 * LX : 0), nA = h ? 2 : 0, dr = h ? -LX : LX;
+        // row walk of this lane
+        const int nA = h ? 2 : 0, nodeB = wbase + (h ? 2 * LX : 0);
         double S[5] = {0.0, 0.0, 0.0, 0.0, 0.0}; // rho, J_x, J_y, J_z, 2 rho E (FP32: deviations)
+        // each round's fields are in flight while the round before is summed
+        LdsT v[2][9];
+        if (stager) fetch(0, v);
 #pragma unroll 1
         for (int szo = 0; szo < 15; ++szo) {
-            const int so = szo / 5, sz = szo - 5 * so;
             __syncthreads();
-            if (stager) {
-                const unsigned off = (ndxy + plane * (unsigned)box.wrap(z + sz - 2, box.nz)) * (unsigned)sizeof(LdsT);
-                LdsT v[2][9];
-#pragma unroll
-                for (int i = 0; i < 9; ++i)
-#pragma unroll
-                    for (int set = 0; set < 2; ++set)
-                        v[set][i] = *(const POND_GLOBAL LdsT *)((const POND_GLOBAL char *)(dmom + (size_t)(27 * set + 3 * i + so) * N) + off);
-#pragma unroll
-                for (int n = 0; n < 3; ++n) {
-                    LdsT f[3], g[3];
-#pragma unroll
-                    for (int m = 0; m < 3; ++m) {
-                        f[m] = v[0][3 * m + n] - (kDev ? ref[9 * m + 3 * n + so] : (LdsT)0);
-                        g[m] = v[1][3 * m + n] - (kDev ? ref[27 + 9 * m + 3 * n + so] : (LdsT)0);
-                    }
-                    SumRow<LdsT>::store(lds, LN, n, tid, f, g);
-                }
-            }
+            if (stager) stage(szo / 5, v, std::true_type{});
             __syncthreads();
+            if (stager && szo < 14) fetch(szo + 1, v);
             LdsT Y[4] = {(LdsT)0, (LdsT)0, (LdsT)0, (LdsT)0};
-#pragma unroll
-            for (int j = 0; j < 5; ++j) row_sums<LdsT>(lds, LN, nA, nodeA + j * dr, a0, a1, b0[j], b1[j], Y);
-#pragma unroll
-            for (int j = 0; j < 3; ++j) row_sums<LdsT>(lds, LN, 1, nodeA + j * dr, a0, a1, b0[5 + j], b1[5 + j], Y);
+            plane_sums<LdsT, LNS, LX>(lds, nA, wbase, nodeB, a0, a1, b0, b1, Y);
             const double g0 = (double)s_cz[(2 * szo) * NR + rcv], g1 = (double)s_cz[(2 * szo + 1) * NR + rcv];
             S[0] += g0 * (double)Y[0];
             S[1] += g0 * (double)Y[1];
@@ -663,46 +725,20 @@ __global__ void __launch_bounds__(2 * TX *TY, sizeof(LdsT) == 4 ? 3 : 2) k3_stre
                 // one round after block z, while it is still in the XCD's L2
                 const int so = szo / 5, sz = szo - 5 * so;
                 __syncthreads();
-                const int zz = box.wrap(z + sz - 2, box.nz);
                 if (stager) {
-                    const unsigned off = (ndxy + plane * (unsigned)zz) * (unsigned)sizeof(LdsT);
-                    // loads in batches of MB fields per set before their stores, so that
-                    // their latencies overlap
-                    constexpr int MB = 9;
-                    static_assert(FPS % MB == 0, "whole batches of fields");
-#pragma unroll
-                    for (int m0 = 0; m0 < FPS; m0 += MB) {
-                        LdsT a[MB], b[MB];
-#pragma unroll
-                        for (int j = 0; j < MB; ++j) {
-                            const int f = 3 * (m0 + j) + so;
-                            a[j] = *(const POND_GLOBAL LdsT *)((const POND_GLOBAL char *)(dmom + (size_t)f * N) + off);
-                            b[j] = *(const POND_GLOBAL LdsT *)((const POND_GLOBAL char *)(dmom + (size_t)(27 + f) * N) + off);
-                        }
-#pragma unroll
-                        for (int j = 0; j < MB; ++j) {
-                            const int f = 3 * (m0 + j) + so;
-                            Pair v;
-                            if (kDev) {
-                                v.x = a[j] - ref[f];
-                                v.y = b[j] - ref[27 + f];
-                            } else {
-                                v.x = a[j];
-                                v.y = b[j];
-                            }
-                            *(Pair *)&lds[((m0 + j) * LN + tid) * 2] = v;
-                        }
-                    }
+                    LdsT v[2][9];
+                    fetch(szo, v);
+                    stage(so, v, std::false_type{});
                 }
                 __syncthreads();
 
-                const LdsT *sbase = &lds[wbase * 2 + myset];
+                const PopRow<LdsT, LN> rows(lds, wbase, myset);
                 AccT Y[3][3];
 #pragma unroll
                 for (int k = 0; k < 3; ++k)
 #pragma unroll
                     for (int l = 0; l < 3; ++l) Y[k][l] = (AccT)0;
-                xy_window<FAST, LdsT, AccT, LN, LX>(sbase, wx, wy, A, B, Y);
+                xy_window<FAST, LdsT, LN, LX>(rows, wx, wy, A, B, Y);
                 // z contraction: departure point m of the receiver takes its z tap of plane sz
                 // times its z Lagrange coefficient of power so
 #pragma unroll
