@@ -43,6 +43,7 @@ int handle_update_desc(pond_handle *h)
     tile_counts(h->lc, &stx, &stc, &fcx, &fcc);
     h->st_tiles = stc;
     h->fc_tiles = fcc;
+    h->lc.lanes = step_lanes(h->lc, stc);
     const int R = h->states();
     for (int p = 0; p < R; ++p) {
         SlotDesc &d = h->desc_h[p];
@@ -183,8 +184,6 @@ bool make_ghost(const pond_config &c, const double st[5], GhostFace &G)
     G.rho = rho;
     G.T = T;
     G.h = e + p / rho;
-    G.mu = (1.0 / c.omega - 0.5) * p * c.dt;
-    G.kc = c.k_scale * G.mu * c.R * (1.0 + c.delta) / c.delta;
     return true;
 }
 

@@ -9,8 +9,16 @@
 
 namespace pond {
 
-// fields of the thermodynamic region of a tile
-enum { kThFx = 0, kThFy, kThT, kThH, kThMu, kThKc, kThP, kThFields };
+// fields of the thermodynamic region of a tile: the force, the heat-flux potential
+// k/p T - mu/p h and the pressure.  mu and k are proportional to the pressure (mu = (1/omega
+// - 1/2) p dt, k = k_scale mu C_p^ig, inflow ghosts included), so the potential and p are all
+// that the heat-flux correction needs of T, h, mu and k.
+enum { kThFx = 0, kThFy, kThQ, kThP, kThFields };
+template <typename PT>
+__device__ __forceinline__ double flux_potential(const PT &P, double visc, double T, double h)
+{
+    return visc * (P.k_scale * P.Cp_ig * T - h);
+}
 
 // ---------------------------------------------------------------------------
 // Streamed-state moment planes (pond_internal.h, "mom") in FP64, or in the mixed form of
@@ -91,8 +99,7 @@ __device__ __forceinline__ void korteweg_force(const double *Kxx, const double *
 
 // Thermodynamic state of a node from its streamed density, gauge velocity, g sum
 // (2 rho E) and force: u-hat = u + F dt/(2 rho), e = E - |u-hat|^2/2, T and p from the
-// EoS, h = e + p/rho, mu = (1/omega - 1/2) p dt, k = k_scale mu C_p^ig.  Writes the
-// fields of an LDS thermodynamic region (field stride `stride`) at index li; returns the
+// EoS, h = e + p/rho, the heat-flux potential (visc = mu/p).  Writes the fields of an LDS thermodynamic region (field stride `stride`) at index li; returns the
 // admissibility bits.  GEN = false: the van der Waals fluid with its energy equation only
 // (the lean variant of the streaming kernels).
 template <int DIM, bool GEN = true, typename PT>
@@ -111,13 +118,9 @@ __device__ __forceinline__ int thermo_state(const PT &P, double rho, double ux, 
     const double T = eos_T_of_e<GEN>(P, rho, e);
     const double p = GEN ? eos_p<GEN>(P, rho, T) : vdw_p_lean(P, rho, T, i_rq);
     const int err = eos_bad<GEN>(P, rho, p);
-    const double mu = visc * p;
     th[kThFx * stride + li] = Fx;
     th[kThFy * stride + li] = Fy;
-    th[kThT * stride + li] = T;
-    th[kThH * stride + li] = e + 2.0 * p * h_r;
-    th[kThMu * stride + li] = mu;
-    th[kThKc * stride + li] = P.k_scale * mu * P.Cp_ig;
+    th[kThQ * stride + li] = flux_potential(P, visc, T, e + 2.0 * p * h_r);
     th[kThP * stride + li] = p;
     return err;
 }
@@ -195,14 +198,14 @@ __device__ __forceinline__ void collide_f(const PT &P, double rho, double i_rho,
 }
 
 // heat-flux correction M0 = 2 div(-mu grad h + k grad T) in flux form (eq. 9), at the
-// position hb of an LDS thermodynamic region of row stride HX and field stride HS
+// position hb of an LDS thermodynamic region of row stride HX and field stride HS: with the
+// link means of mu and k proportional to that of p, k dT - mu dh = p d(potential) per link
 template <int DIM, typename PT>
 __device__ __forceinline__ double heat_correction(const PT &P, const double *th, int HS, int hb, int HX)
 {
     constexpr int Q = Layout<DIM>::Q;
     if (!(P.k_scale >= 0.0)) return 0.0;
-    const double T0 = th[kThT * HS + hb], h0 = th[kThH * HS + hb];
-    const double m0 = th[kThMu * HS + hb], k0 = th[kThKc * HS + hb];
+    const double q0 = th[kThQ * HS + hb], p0 = th[kThP * HS + hb];
     double acc = 0.0;
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
@@ -210,9 +213,7 @@ __device__ __forceinline__ double heat_correction(const PT &P, const double *th,
         const int ey = DIM == 2 ? q % 3 - 1 : 0;
         const double w = DIM == 2 ? kW1[q / 3] * kW1[q % 3] : kW1[q];
         const int k = hb + ex + ey * HX;
-        const double kmid = 0.5 * (th[kThKc * HS + k] + k0);
-        const double mmid = 0.5 * (th[kThMu * HS + k] + m0);
-        acc += w * (kmid * (th[kThT * HS + k] - T0) - mmid * (th[kThH * HS + k] - h0));
+        acc += (0.5 * w) * (th[kThP * HS + k] + p0) * (th[kThQ * HS + k] - q0);
     }
     return 2.0 * (2.0 * kInvTL) * acc;
 }

@@ -320,12 +320,12 @@ __device__ __forceinline__ int window_weights(double u, double s, double dt, T w
         const double v = u + s * (double)(k - 1);
         const double d = -v * dt;            // displacement of the departure point
         const double fl = floor(d);
-        const double t = d - fl + 1.0;       // coordinate inside the 4-node stencil
+        const double x = d - fl;             // position in the stencil's middle cell
         int i0 = (int)fl;                    // stencil nodes i0-1 .. i0+2
-        const double w0 = -(t - 1.0) * (t - 2.0) * (t - 3.0) * (1.0 / 6.0);
-        const double w1 = t * (t - 2.0) * (t - 3.0) * 0.5;
-        const double w2 = -t * (t - 1.0) * (t - 3.0) * 0.5;
-        const double w3 = t * (t - 1.0) * (t - 2.0) * (1.0 / 6.0);
+        // cubic Lagrange weights of the nodes -1, 0, 1, 2 at x, by their common factors
+        const double xm = x - 1.0, xp = x + 1.0, x2 = x - 2.0;
+        const double a = x * xm * (1.0 / 6.0), b = xp * x2 * 0.5;
+        const double w0 = -a * x2, w1 = b * xm, w2 = -b * x, w3 = a * xp;
         if (i0 < -1 || i0 > 0) {
             bad = kErrHalo;
             i0 = i0 < -1 ? -1 : 0;

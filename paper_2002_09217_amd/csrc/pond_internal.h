@@ -30,7 +30,7 @@ constexpr int kFusedRun = 45;
 struct GhostFace {
     double f[9], g[9];     // populations, same index convention as the lattice
     double ux, uy, theta;  // gauge
-    double rho, T, h, mu, kc;
+    double rho, T, h;
 };
 
 // Per-lattice parameters, resident in device memory and read through a pointer.
@@ -152,6 +152,8 @@ struct LaunchCtx {
     // planes, mixed FP64/FP32 in the FP32 storage precisions); false: two kernels per
     // step with stored populations
     bool fused = false;
+    // lanes per receiver of the streaming and fused-step kernels (step_lanes)
+    int lanes = 2;
 };
 
 int stream_variants(int dim);
@@ -176,6 +178,9 @@ hipError_t launch_step_double_windows(const LaunchCtx &c, const SlotDesc *slots,
 // fused step: closure of the state in `mom` (every node), raising its errors with
 // kErrCollideStage and counting as a launch; `tiles` as for launch_force_collide
 hipError_t launch_collide_check(const LaunchCtx &c, const SlotDesc *slots, int nslots, int tiles);
+// lanes per receiver for a lattice of `tiles` tiles of the current shape: a choice of the
+// lattice alone, so that it runs the same kernel by itself and in a batch
+int step_lanes(const LaunchCtx &c, int tiles);
 // tile counts of one lattice for the current tile shapes
 void tile_counts(const LaunchCtx &c, int *st_tiles_x, int *st_count, int *fc_tiles_x, int *fc_count);
 hipError_t launch_korteweg(const LaunchCtx &c, const DevState &s, const double *rho);

@@ -77,11 +77,9 @@ hipError_t launch_gather_slot_flags(hipStream_t st, const SlotDesc *slots, int n
 // ---------------------------------------------------------------------------
 // streaming with the predictor-corrector
 // ---------------------------------------------------------------------------
-// Two lanes per receiver: lane 2 i + set works on population set `set` (0 = f, 1 = g)
-// of receiver i; the pass moments are exchanged between the two lanes.  Blocks of at
-// most 256 lanes are compiled for three waves per SIMD, larger ones for two.
-template <int DIM, typename PopT, typename LdsT, int TX, int TY, bool GEN>
-__global__ void __launch_bounds__(2 * TX *TY, 2 * TX *TY <= 256 ? 3 : 2)
+// LANES lanes per receiver (step_lanes); the fill uses all lanes of the block
+template <int DIM, int LANES, typename PopT, typename LdsT, int TX, int TY, bool GEN>
+__global__ void __launch_bounds__(LANES *TX *TY, sizeof(LdsT) == 4 ? 3 : 2)
     k_stream(const SlotDesc *__restrict__ slots, int nslots)
 {
     using L = Layout<DIM>;
@@ -89,12 +87,8 @@ __global__ void __launch_bounds__(2 * TX *TY, 2 * TX *TY <= 256 ? 3 : 2)
     constexpr int LX = TX + 2 * H;
     constexpr int LY = DIM == 2 ? TY + 2 * H : 1;
     constexpr int LN = LX * LY;
-    constexpr int NT = 2 * TX * TY;
-    // Moment fields of the tile.  The two sets of a node are adjacent (index
-    // ((mn LN + node) 2 + set)), so the two lanes of a receiver and neighbouring
-    // receivers read one contiguous run of LDS words: no bank conflicts.
-    constexpr int CS = 2;                                         // column stride
-    __shared__ LdsT lds[2 * NF * LN];
+    constexpr int NT = LANES * TX * TY;
+    __shared__ __align__(16) LdsT lds[2 * NF * LN]; // moment fields of the tile (pair_at)
     __shared__ int abort_block;
 
     // lattice and tile of this workgroup
@@ -109,7 +103,7 @@ __global__ void __launch_bounds__(2 * TX *TY, 2 * TX *TY <= 256 ? 3 : 2)
     // Error state of earlier steps: read now, acted on after the fill (which only reads),
     // so that its latency overlaps the fill's loads.  The decision is taken once per
     // block, so every wave of the block leaves together.
-    const int tid = threadIdx.x + 2 * TX * threadIdx.y;
+    const int tid = threadIdx.x;
     int err_before = 0;
     if (tid == 0) err_before = flags[kFlagErr];
     const POND_GLOBAL DevParams &P = *(const POND_GLOBAL DevParams *)S.P;
@@ -142,10 +136,8 @@ __global__ void __launch_bounds__(2 * TX *TY, 2 * TX *TY <= 256 ? 3 : 2)
     }
 
     // the receiver's own gauge and force, loaded now so that the latency overlaps the fill
-    const int lxr = (int)threadIdx.x >> 1;
-    const int myset = (int)threadIdx.x & 1;
-    const int gx = bx0 + lxr;
-    const int gy = by0 + (DIM == 2 ? threadIdx.y : 0);
+    const int half = lane_half<LANES>(tid), lxr = lane_receiver<LANES>(tid) % TX, lyr = lane_receiver<LANES>(tid) / TX;
+    const int gx = bx0 + lxr, gy = by0 + lyr;
     const bool inside = gx < P.nx && (DIM == 1 || gy < P.ny);
     const int node = inside ? gx + P.nx * gy : cnode;
     double Ux = side[kSideUx * N + node];
@@ -211,7 +203,7 @@ __global__ void __launch_bounds__(2 * TX *TY, 2 * TX *TY <= 256 ? 3 : 2)
             }
         }
 #pragma unroll
-        for (int i = 0; i < NF; ++i) lds[(i * LN + r.li) * 2 + r.set] = (LdsT)m[i];
+        for (int i = 0; i < NF; ++i) lds[pair_at<DIM, LdsT, LN>(i, r.li) + r.set] = (LdsT)m[i];
     };
     for (int it = tid; it < NITEMS; it += 2 * NT) {
         Raw ra, rb;
@@ -232,39 +224,43 @@ __global__ void __launch_bounds__(2 * TX *TY, 2 * TX *TY <= 256 ? 3 : 2)
 
     // both lanes of a receiver leave together, so the exchanges below always pair up
     if (!inside) return;
-    const int wbase = (DIM == 2 ? threadIdx.y * LX : 0) + lxr; // window (gx-2, gy-2)
-    const double dt = P.dt;
+    const int wbase = lyr * LX + lxr; // window (gx-2, gy-2)
 
-    // this lane's set of the receiver, in the gauge (sUx, sUy, sS) of the last pass
-    double pq[Q];
+    // the populations of the receiver in the gauge (sUx, sUy, sS) of the last pass
+    double f[Q], g[Q];
     double sUx = Ux, sUy = Uy, sS = 1.0;
     double rho = 0.0;
-    int err = 0;
-    const LdsT *sbase = &lds[wbase * 2 + myset];
-    err |= stream_passes<DIM, LdsT, LN, LX, NT, GEN>(P, sbase, tid, myset, rx, ry, refR0, refR1, refT, Ux, Uy, th,
-                                                     Fpx, Fpy, pq, rho, sUx, sUy, sS);
-
-    store_streamed<DIM, false>(S.mom, N, node, myset, pq, rho, Ux, Uy, sUx, sUy, sS);
+    const int err = stream_passes<DIM, LANES, LdsT, LN, LX, NT, GEN>(P, lds, wbase, tid, half, rx, ry, refR0, refR1, refT,
+                                                                     Ux, Uy, th, Fpx, Fpy, f, g, rho, sUx, sUy, sS);
+    store_streamed<DIM, false>(S.mom, N, node, half, f, rho, Ux, Uy, sUx, sUy, sS);
+    if (LANES == 1) store_streamed<DIM, false>(S.mom, N, node, 1, g, rho, Ux, Uy, sUx, sUy, sS);
     if (err) raise_error(flags, err, S.parity);
 }
 
-template <int DIM, typename PopT, typename LdsT, int TX, int TY, bool GEN>
+template <int DIM, int LANES, typename PopT, typename LdsT, int TX, int TY, bool GEN>
 static hipError_t launch_stream_g(const LaunchCtx &c, const SlotDesc *slots, int nslots, int tiles)
 {
-    dim3 block(2 * TX, TY);
+    dim3 block(LANES * TX * TY);
     if (c.ev_start)
-        hipExtLaunchKernelGGL((k_stream<DIM, PopT, LdsT, TX, TY, GEN>), dim3(tiles), block, 0, c.st,
+        hipExtLaunchKernelGGL((k_stream<DIM, LANES, PopT, LdsT, TX, TY, GEN>), dim3(tiles), block, 0, c.st,
                               c.ev_start, c.ev_stop, 0, slots, nslots);
     else
-        hipLaunchKernelGGL((k_stream<DIM, PopT, LdsT, TX, TY, GEN>), dim3(tiles), block, 0, c.st, slots,
+        hipLaunchKernelGGL((k_stream<DIM, LANES, PopT, LdsT, TX, TY, GEN>), dim3(tiles), block, 0, c.st, slots,
                            nslots);
     return hipGetLastError();
 }
-template <int DIM, typename PopT, typename LdsT, int TX, int TY>
+template <int DIM, int LANES, typename PopT, typename LdsT, int TX, int TY>
 static hipError_t launch_stream_t(const LaunchCtx &c, const SlotDesc *slots, int nslots, int tiles)
 {
-    return c.gen_eos ? launch_stream_g<DIM, PopT, LdsT, TX, TY, true>(c, slots, nslots, tiles)
-                     : launch_stream_g<DIM, PopT, LdsT, TX, TY, false>(c, slots, nslots, tiles);
+    return c.gen_eos ? launch_stream_g<DIM, LANES, PopT, LdsT, TX, TY, true>(c, slots, nslots, tiles)
+                     : launch_stream_g<DIM, LANES, PopT, LdsT, TX, TY, false>(c, slots, nslots, tiles);
+}
+template <typename PopT, typename LdsT, int TX, int TY>
+static hipError_t launch_stream_l(const LaunchCtx &c, const SlotDesc *slots, int nslots, int tiles)
+{
+    if constexpr (TX * TY == 256 && TY >= 8) // the shapes of step_lanes
+        if (c.lanes == 1) return launch_stream_t<2, 1, PopT, LdsT, TX, TY>(c, slots, nslots, tiles);
+    return launch_stream_t<2, 2, PopT, LdsT, TX, TY>(c, slots, nslots, tiles);
 }
 
 // Tile shapes of the streaming kernel (receivers per block, x by y); the library picks
@@ -288,16 +284,16 @@ static hipError_t launch_stream_v(const LaunchCtx &c, const SlotDesc *slots, int
 {
     if (c.dim == 2) {
         switch (c.stream_tile) {
-        case 1: return launch_stream_t<2, PopT, LdsT, 32, 4>(c, slots, nslots, tiles);
-        case 2: return launch_stream_t<2, PopT, LdsT, 16, 8>(c, slots, nslots, tiles);
-        case 3: return launch_stream_t<2, PopT, LdsT, 64, 4>(c, slots, nslots, tiles);
-        case 4: return launch_stream_t<2, PopT, LdsT, 16, 4>(c, slots, nslots, tiles);
-        case 5: return launch_stream_t<2, PopT, LdsT, 16, 16>(c, slots, nslots, tiles);
-        default: return launch_stream_t<2, PopT, LdsT, 32, 8>(c, slots, nslots, tiles);
+        case 1: return launch_stream_l<PopT, LdsT, 32, 4>(c, slots, nslots, tiles);
+        case 2: return launch_stream_l<PopT, LdsT, 16, 8>(c, slots, nslots, tiles);
+        case 3: return launch_stream_l<PopT, LdsT, 64, 4>(c, slots, nslots, tiles);
+        case 4: return launch_stream_l<PopT, LdsT, 16, 4>(c, slots, nslots, tiles);
+        case 5: return launch_stream_l<PopT, LdsT, 16, 16>(c, slots, nslots, tiles);
+        default: return launch_stream_l<PopT, LdsT, 32, 8>(c, slots, nslots, tiles);
         }
     }
-    if (c.stream_tile == 1) return launch_stream_t<1, PopT, LdsT, 64, 1>(c, slots, nslots, tiles);
-    return launch_stream_t<1, PopT, LdsT, 128, 1>(c, slots, nslots, tiles);
+    if (c.stream_tile == 1) return launch_stream_t<1, 2, PopT, LdsT, 64, 1>(c, slots, nslots, tiles);
+    return launch_stream_t<1, 2, PopT, LdsT, 128, 1>(c, slots, nslots, tiles);
 }
 
 hipError_t launch_stream(const LaunchCtx &c, const SlotDesc *slots, int nslots, int tiles)
@@ -407,7 +403,7 @@ __device__ __forceinline__ void korteweg_force_at(const PT &P, const double *__r
 // Fused non-local closure and collision of one tile (eqs. 9, 16-22; App. F):
 //   LDS stage 1  rho on the tile + 3-node halo (from the streamed state)
 //   LDS stage 2  Korteweg stress K on the tile + 2-node halo
-//   LDS stage 3  F = -div K, actual velocity, T, p, h, mu, k on the tile + 1-node halo
+//   LDS stage 3  F = -div K, actual velocity, T, p, h on the tile + 1-node halo
 //   per node     heat-flux correction M0, re-expression of the streamed state in the
 //                collision gauge (u, theta), BGK collision of f (force source S) and g
 //                (force-extended equilibrium, sources g~ + phi); writes the new state.
@@ -595,10 +591,8 @@ __global__ void __launch_bounds__(2 * TX *TY)
             err |= thermo_state<DIM>(P, rho, pre_u[j][0], pre_u[j][1], pre_u[j][2], Fx, Fy, visc, s_th, HS, li);
         } else if (cls == kGhost) {
             const POND_GLOBAL GhostFace &G = P.ghost[face];
-            s_th[kThT * HS + li] = G.T;
-            s_th[kThH * HS + li] = G.h;
-            s_th[kThMu * HS + li] = G.mu;
-            s_th[kThKc * HS + li] = G.kc;
+            s_th[kThQ * HS + li] = flux_potential(P, visc, G.T, G.h);
+            s_th[kThP * HS + li] = G.rho * G.theta * kTL;
         }
     }
     if (MODE == kCollideCheck) {
@@ -699,6 +693,21 @@ hipError_t launch_collide_check(const LaunchCtx &c, const SlotDesc *slots, int n
                      : launch_force_collide_t<2, double, false, kCollideCheck>(c, slots, nslots, tiles);
     return mixed ? launch_force_collide_t<1, float, true, kCollideCheck>(c, slots, nslots, tiles)
                  : launch_force_collide_t<1, double, false, kCollideCheck>(c, slots, nslots, tiles);
+}
+
+// Two lanes a receiver fill a CU with one 512-lane workgroup, which is as much as there is up
+// to one tile per CU: 256^2 FP64 18.7 us against 20.2 with one lane.  Beyond that one lane
+// leaves the receiver's weights to be computed once and two or three 256-lane workgroups to
+// overlap on a CU: 2048^2 878 us against 1224 (FP64, 16 x 16), 702 against 1103 (FP32).
+// Tiles of fewer receivers would leave workgroups of two waves (16 x 8: 1072 us), and two 64 x
+// 4 tiles do not fit a CU's LDS in FP64.
+static bool one_lane_shape(int tx, int ty) { return tx * ty == 256 && ty >= 8; }
+int step_lanes(const LaunchCtx &c, int tiles)
+{
+    int tx, ty;
+    if (c.dim != 2) return 2;
+    stream_tile_shape(c.dim, c.stream_tile, &tx, &ty);
+    return one_lane_shape(tx, ty) && tiles > kCUs ? 1 : 2;
 }
 
 void tile_counts(const LaunchCtx &c, int *st_tiles_x, int *st_count, int *fc_tiles_x, int *fc_count)

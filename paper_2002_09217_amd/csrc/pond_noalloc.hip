@@ -92,6 +92,7 @@ extern "C" int pond_step_noalloc(const pond_config *cfg, void *state0, void *sta
     lc.gen_eos = c.eos != POND_EOS_VDW || c.isothermal;
     int stx, stc, fcx, fcc;
     tile_counts(lc, &stx, &stc, &fcx, &fcc);
+    lc.lanes = step_lanes(lc, stc);
 
     // a state buffer: the population planes, then the side planes
     const size_t popb = state_pop_bytes(c.dim, N, lc.fp32);

@@ -31,16 +31,15 @@
 
 namespace pond {
 
-// Two lanes per receiver (lane 2 i + set), as in k_stream; blocks of at most 256 lanes
-// are compiled for three waves per SIMD, larger ones for two.
-template <int DIM, bool MIXED, typename LdsT, int TX, int TY, bool GEN>
-__global__ void __launch_bounds__(2 * TX *TY, 2 * TX *TY <= 256 ? 3 : 2)
+// LANES lanes per receiver; the stages before the streaming use all lanes of the block
+template <int DIM, int LANES, bool MIXED, typename LdsT, int TX, int TY, bool GEN>
+__global__ void __launch_bounds__(LANES *TX *TY, sizeof(LdsT) == 4 ? 3 : 2)
     k_step(const SlotDesc *__restrict__ slots, int nslots)
 {
     using L = Layout<DIM>;
     using MIO = MomIO<DIM, MIXED>;
     constexpr int Q = L::Q, NF = L::NF;
-    constexpr int NT = 2 * TX * TY;
+    constexpr int NT = LANES * TX * TY;
     constexpr int LX = TX + 4, LY = DIM == 2 ? TY + 4 : 1, LN = LX * LY;   // donors: halo 2
     constexpr int HX = TX + 6, HY = DIM == 2 ? TY + 6 : 1, HN = HX * HY;   // closure: halo 3
     constexpr int KX = TX + 8, KY = DIM == 2 ? TY + 8 : 1, KN = KX * KY;   // stress: halo 4
@@ -63,7 +62,7 @@ __global__ void __launch_bounds__(2 * TX *TY, 2 * TX *TY <= 256 ? 3 : 2)
     const int tile = gtile - S.st_begin;
     int *__restrict__ flags = S.flags;
     const void *msrc = S.smom_src;
-    const int tid = threadIdx.x + 2 * TX * threadIdx.y;
+    const int tid = threadIdx.x;
     int err_before = 0;
     if (tid == 0) err_before = flags[kFlagErr];
     const POND_GLOBAL DevParams &P = *(const POND_GLOBAL DevParams *)S.P;
@@ -91,10 +90,8 @@ __global__ void __launch_bounds__(2 * TX *TY, 2 * TX *TY <= 256 ? 3 : 2)
     const double refR1 = kDevI ? MIO::load(msrc, N, cnode, L::kG) : 0.0; // the streamed g sum
 
     // this lane's receiver and its own streamed state
-    const int lxr = (int)threadIdx.x >> 1;
-    const int myset = (int)threadIdx.x & 1;
-    const int gx = bx0 + lxr;
-    const int gy = by0 + (DIM == 2 ? threadIdx.y : 0);
+    const int half = lane_half<LANES>(tid), lxr = lane_receiver<LANES>(tid) % TX, lyr = lane_receiver<LANES>(tid) / TX;
+    const int gx = bx0 + lxr, gy = by0 + lyr;
     const bool inside = gx < P.nx && (DIM == 1 || gy < P.ny);
     const int node = inside ? gx + P.nx * gy : cnode;
     double Ux = MIO::load(msrc, N, node, L::kUx);
@@ -222,10 +219,8 @@ __global__ void __launch_bounds__(2 * TX *TY, 2 * TX *TY <= 256 ? 3 : 2)
             err_c |= thermo_state<DIM, GEN>(P, rho, pre_c[j][1], pre_c[j][2], pre_c[j][3], Fx, Fy, visc, s_th, HN, li);
         } else if (cls == kGhost) {
             const POND_GLOBAL GhostFace &G = P.ghost[face];
-            s_th[kThT * HN + li] = G.T;
-            s_th[kThH * HN + li] = G.h;
-            s_th[kThMu * HN + li] = G.mu;
-            s_th[kThKc * HN + li] = G.kc;
+            s_th[kThQ * HN + li] = flux_potential(P, visc, G.T, G.h);
+            s_th[kThP * HN + li] = G.rho * G.theta * kTL;
         }
     }
     __syncthreads();
@@ -310,7 +305,7 @@ __global__ void __launch_bounds__(2 * TX *TY, 2 * TX *TY <= 256 ? 3 : 2)
                 LdsT2 v;
                 v.x = (LdsT)mf[i];
                 v.y = (LdsT)mg[i];
-                *(LdsT2 *)&lds[(i * LN + li) * 2] = v;
+                *(LdsT2 *)&lds[pair_at<DIM, LdsT, LN>(i, li)] = v;
             }
         }
     }
@@ -322,10 +317,8 @@ __global__ void __launch_bounds__(2 * TX *TY, 2 * TX *TY <= 256 ? 3 : 2)
             if (classify<DIM>(geo, bx0 - 2 + wx, by0 - 2 + wy, cx, cy, face) == kCopy) {
                 const int src = (cx - (bx0 - 2)) + (DIM == 2 ? (cy - (by0 - 2)) * LX : 0);
 #pragma unroll
-                for (int i = 0; i < NF; ++i) {
-                    lds[(i * LN + li) * 2] = lds[(i * LN + src) * 2];
-                    lds[(i * LN + li) * 2 + 1] = lds[(i * LN + src) * 2 + 1];
-                }
+                for (int i = 0; i < NF; ++i)
+                    *(LdsT2 *)&lds[pair_at<DIM, LdsT, LN>(i, li)] = *(const LdsT2 *)&lds[pair_at<DIM, LdsT, LN>(i, src)];
             }
         }
         __syncthreads();
@@ -335,38 +328,46 @@ __global__ void __launch_bounds__(2 * TX *TY, 2 * TX *TY <= 256 ? 3 : 2)
     // both lanes of a receiver leave together, so the exchanges always pair up
     if (!inside) return;
     // the receiver's gauge and force: its collision of the streamed state
-    const int hr = (DIM == 2 ? (threadIdx.y + 3) * HX : 0) + lxr + 3;
+    const int hr = (DIM == 2 ? (lyr + 3) * HX : 0) + lxr + 3;
     double th = s_th[kThP * HN + hr] * (1.0 / rho_own) * kInvTL;
     const double Fpx = s_th[kThFx * HN + hr];
     const double Fpy = DIM == 2 ? s_th[kThFy * HN + hr] : 0.0;
-    const int wbase = (DIM == 2 ? threadIdx.y * LX : 0) + lxr; // window (gx-2, gy-2)
-    const LdsT *sbase = &lds[wbase * 2 + myset];
-    double pq[Q];
+    const int wbase = lyr * LX + lxr; // window (gx-2, gy-2)
+    double f[Q], g[Q];
     double sUx = Ux, sUy = Uy, sS = 1.0;
     double rho = 0.0;
-    const int err = stream_passes<DIM, LdsT, LN, LX, NT, GEN>(P, sbase, tid, myset, rx, ry, refR0, refR1, refT, Ux,
-                                                              Uy, th, Fpx, Fpy, pq, rho, sUx, sUy, sS);
-    store_streamed<DIM, MIXED>(S.smom_dst, N, node, myset, pq, rho, Ux, Uy, sUx, sUy, sS);
+    const int err = stream_passes<DIM, LANES, LdsT, LN, LX, NT, GEN>(P, lds, wbase, tid, half, rx, ry, refR0, refR1, refT,
+                                                                     Ux, Uy, th, Fpx, Fpy, f, g, rho, sUx, sUy, sS);
+    store_streamed<DIM, MIXED>(S.smom_dst, N, node, half, f, rho, Ux, Uy, sUx, sUy, sS);
+    if (LANES == 1) store_streamed<DIM, MIXED>(S.smom_dst, N, node, 1, g, rho, Ux, Uy, sUx, sUy, sS);
     if (err) raise_error(flags, err, S.parity);
 }
 
-template <int DIM, bool MIXED, typename LdsT, int TX, int TY, bool GEN>
+template <int DIM, int LANES, bool MIXED, typename LdsT, int TX, int TY, bool GEN>
 static hipError_t launch_step_g(const LaunchCtx &c, const SlotDesc *slots, int nslots, int tiles)
 {
-    dim3 block(2 * TX, TY);
+    dim3 block(LANES * TX * TY);
     if (c.ev_start)
-        hipExtLaunchKernelGGL((k_step<DIM, MIXED, LdsT, TX, TY, GEN>), dim3(tiles), block, 0, c.st, c.ev_start,
+        hipExtLaunchKernelGGL((k_step<DIM, LANES, MIXED, LdsT, TX, TY, GEN>), dim3(tiles), block, 0, c.st, c.ev_start,
                               c.ev_stop, 0, slots, nslots);
     else
-        hipLaunchKernelGGL((k_step<DIM, MIXED, LdsT, TX, TY, GEN>), dim3(tiles), block, 0, c.st, slots, nslots);
+        hipLaunchKernelGGL((k_step<DIM, LANES, MIXED, LdsT, TX, TY, GEN>), dim3(tiles), block, 0, c.st, slots, nslots);
     return hipGetLastError();
 }
 
-template <int DIM, bool MIXED, typename LdsT, int TX, int TY>
+template <int DIM, int LANES, bool MIXED, typename LdsT, int TX, int TY>
 static hipError_t launch_step_t(const LaunchCtx &c, const SlotDesc *slots, int nslots, int tiles)
 {
-    return c.gen_eos ? launch_step_g<DIM, MIXED, LdsT, TX, TY, true>(c, slots, nslots, tiles)
-                     : launch_step_g<DIM, MIXED, LdsT, TX, TY, false>(c, slots, nslots, tiles);
+    return c.gen_eos ? launch_step_g<DIM, LANES, MIXED, LdsT, TX, TY, true>(c, slots, nslots, tiles)
+                     : launch_step_g<DIM, LANES, MIXED, LdsT, TX, TY, false>(c, slots, nslots, tiles);
+}
+
+template <bool MIXED, typename LdsT, int TX, int TY>
+static hipError_t launch_step_l(const LaunchCtx &c, const SlotDesc *slots, int nslots, int tiles)
+{
+    if constexpr (TX * TY == 256 && TY >= 8) // the shapes of step_lanes
+        if (c.lanes == 1) return launch_step_t<2, 1, MIXED, LdsT, TX, TY>(c, slots, nslots, tiles);
+    return launch_step_t<2, 2, MIXED, LdsT, TX, TY>(c, slots, nslots, tiles);
 }
 
 // the tile shapes of k_stream (stream_tile_shape), same indices
@@ -375,16 +376,16 @@ static hipError_t launch_step_v(const LaunchCtx &c, const SlotDesc *slots, int n
 {
     if (c.dim == 2) {
         switch (c.stream_tile) {
-        case 1: return launch_step_t<2, MIXED, LdsT, 32, 4>(c, slots, nslots, tiles);
-        case 2: return launch_step_t<2, MIXED, LdsT, 16, 8>(c, slots, nslots, tiles);
-        case 3: return launch_step_t<2, MIXED, LdsT, 64, 4>(c, slots, nslots, tiles);
-        case 4: return launch_step_t<2, MIXED, LdsT, 16, 4>(c, slots, nslots, tiles);
-        case 5: return launch_step_t<2, MIXED, LdsT, 16, 16>(c, slots, nslots, tiles);
-        default: return launch_step_t<2, MIXED, LdsT, 32, 8>(c, slots, nslots, tiles);
+        case 1: return launch_step_l<MIXED, LdsT, 32, 4>(c, slots, nslots, tiles);
+        case 2: return launch_step_l<MIXED, LdsT, 16, 8>(c, slots, nslots, tiles);
+        case 3: return launch_step_l<MIXED, LdsT, 64, 4>(c, slots, nslots, tiles);
+        case 4: return launch_step_l<MIXED, LdsT, 16, 4>(c, slots, nslots, tiles);
+        case 5: return launch_step_l<MIXED, LdsT, 16, 16>(c, slots, nslots, tiles);
+        default: return launch_step_l<MIXED, LdsT, 32, 8>(c, slots, nslots, tiles);
         }
     }
-    if (c.stream_tile == 1) return launch_step_t<1, MIXED, LdsT, 64, 1>(c, slots, nslots, tiles);
-    return launch_step_t<1, MIXED, LdsT, 128, 1>(c, slots, nslots, tiles);
+    if (c.stream_tile == 1) return launch_step_t<1, 2, MIXED, LdsT, 64, 1>(c, slots, nslots, tiles);
+    return launch_step_t<1, 2, MIXED, LdsT, 128, 1>(c, slots, nslots, tiles);
 }
 
 // This file is compiled twice (build.py): once for the FP32 windows and the dispatcher,

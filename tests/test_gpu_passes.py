@@ -1,15 +1,18 @@
 """The streaming passes of the predictor-corrector against the oracle, by their number: one
 pass runs the last pass alone (populations), more put the passes that only sum the
-moments of the next gauge before it.  Boxes ragged against the tiles and narrower than
+moments of the next gauge before it.  Lattices ragged against the tiles and narrower than
 the stencil, with a flow fast enough that the stencils of a workgroup do not agree.
 
 Tolerances: FP64 repeats the oracle's sums in another order (1e-12, the parity bound of
 the other FP64 tests), the FP32 forms have the bounds of their box tests: 1e-6 where only
 the stored deviations are rounded, 1e-4 where the window arithmetic is too."""
+import functools
+
+import numpy as np
 import pytest
 
 from paper_2002_09217_amd import pond, workloads as W
-from tests.common import compare, run_gpu, run_oracle3
+from tests.common import compare, pond_config, run_gpu, run_oracle, run_oracle3
 
 pytestmark = pytest.mark.gpu
 
@@ -30,3 +33,46 @@ def test_passes_in_three_dimensions(n, n_pass, precision):
     case = W.perturbed3(*n, seed=5, u0=(0.3, -0.47, 0.2), kappa=0.0176, n_pass=n_pass)
     check(run_oracle3(case, 4), run_gpu(case, 4, precision), ("rho", "ux", "uy", "uz", "E", "T", "p"), TOL[precision],
           case.name)
+
+
+@functools.lru_cache(maxsize=None)
+def shear(n_pass):
+    """A sheared flow, subsonic in some rows and supersonic in others, with an inflow and an
+    outflow face: 288 tiles of 16 x 16 or 32 x 8, more than one a compute unit (the kernels
+    with one lane a receiver), ragged on both sides.  With the oracle's fields after 3 steps."""
+    nx, ny = 275, 250
+    case = W.perturbed(nx, ny, seed=21, rho0=1.0, t_over_tcr=1.4, kappa=0.0176, n_pass=n_pass, dt=0.2)
+    case.u[0] = 0.4 + 0.8 * np.sin(2.0 * np.pi * np.arange(ny) / ny).repeat(nx)
+    case.bc = ((W.INFLOW, W.OUTFLOW), (W.PERIODIC, W.PERIODIC))
+    case.inflow = ((0, 0, (1.0, 0.4, 0.0, 1.4 * W.T_CR)),)
+    return case, run_oracle(case, 3)
+
+
+@pytest.mark.parametrize("precision", list(TOL))
+@pytest.mark.parametrize("two_kernel", [0, 1])
+@pytest.mark.parametrize("tile", [0, 5])
+@pytest.mark.parametrize("n_pass", [1, 2, 3])
+def test_passes_with_one_lane_a_receiver(n_pass, tile, two_kernel, precision):
+    print(f"2d n_pass {n_pass} tile {tile} two_kernel {two_kernel} precision {precision}", flush=True)
+    case, ref = shear(n_pass)
+    got = run_gpu(case, 3, precision, tile=tile, two_kernel=two_kernel)
+    check(ref, got, ("rho", "ux", "uy", "E", "T", "p"), TOL[precision], case.name)
+
+
+@pytest.mark.parametrize("precision", [pond.FP64, pond.FP32_STORE])
+def test_batch_mixes_lanes_a_receiver(precision):
+    """Members of one tile shape, one above and one below a tile a compute unit: each runs the
+    kernel that it runs alone, so the results are the same bits."""
+    cases = [shear(2)[0], W.perturbed(70, 33, seed=2, kappa=0.0176)]
+    print(f"batch precision {precision}", flush=True)
+    alone = [run_gpu(c, 7, precision, tile=5) for c in cases]
+    lats = [pond.Lattice(pond_config(c, precision, tile=5)).init_fields(c.rho, c.u, c.T) for c in cases]
+    with pond.Batch() as batch:
+        for lat in lats:
+            batch.add(lat)
+        assert batch.step(7) == []
+        for lat, ref in zip(lats, alone):
+            got = lat.moments()
+            assert all(np.array_equal(got[k], ref[k]) for k in ref)
+    for lat in lats:
+        lat.close()
