@@ -100,24 +100,24 @@ __device__ __forceinline__ void korteweg_force(const double *Kxx, const double *
 // Thermodynamic state of a node from its streamed density, gauge velocity, g sum
 // (2 rho E) and force: u-hat = u + F dt/(2 rho), e = E - |u-hat|^2/2, T and p from the
 // EoS, h = e + p/rho, the heat-flux potential (visc = mu/p).  Writes the fields of an LDS thermodynamic region (field stride `stride`) at index li; returns the
-// admissibility bits.  GEN = false: the van der Waals fluid with its energy equation only
+// admissibility bits.  LAW = kLean: the van der Waals fluid with its energy equation only
 // (the lean variant of the streaming kernels).
-template <int DIM, bool GEN = true, typename PT>
+template <int DIM, int LAW = kAnyLaw, typename PT>
 __device__ __forceinline__ int thermo_state(const PT &P, double rho, double ux, double uy, double G0, double Fx,
                                             double Fy, double visc, double *th, int stride, int li)
 {
     const double dt = P.dt;
     // van der Waals without the generic laws: one division gives 1 / rho and 1 / (1 - b rho)
     const double q = 1.0 - P.b * rho;
-    const double i_rq = GEN ? 0.0 : 1.0 / (rho * q);
-    const double h_r = GEN ? 0.5 / rho : 0.5 * q * i_rq;
+    const double i_rq = LAW != kLean ? 0.0 : 1.0 / (rho * q);
+    const double h_r = LAW != kLean ? 0.5 / rho : 0.5 * q * i_rq;
     const double E = G0 * h_r;
     const double uhx = ux + Fx * dt * h_r;
     const double uhy = DIM == 2 ? uy + Fy * dt * h_r : 0.0;
     const double e = E - 0.5 * (uhx * uhx + uhy * uhy);
-    const double T = eos_T_of_e<GEN>(P, rho, e);
-    const double p = GEN ? eos_p<GEN>(P, rho, T) : vdw_p_lean(P, rho, T, i_rq);
-    const int err = eos_bad<GEN>(P, rho, p);
+    const double T = eos_T_of_e<LAW>(P, rho, e);
+    const double p = LAW != kLean ? eos_p<LAW>(P, rho, T) : vdw_p_lean(P, rho, T, i_rq);
+    const int err = eos_bad<LAW>(P, rho, p);
     th[kThFx * stride + li] = Fx;
     th[kThFy * stride + li] = Fy;
     th[kThQ * stride + li] = flux_potential(P, visc, T, e + 2.0 * p * h_r);

@@ -42,17 +42,20 @@ constexpr bool kDeviationStore = sizeof(PopT) == 4;
 // pond_eos.h) run with the energy equation or isothermally; the double-well pressure
 // runs isothermally.  Isothermal runs take T = T0 wherever a temperature is needed, and
 // the energy population is passive, carrying e(rho, T0) of the law (C_v T for the
-// double well).  The kind is uniform over a launch, so the branches are scalar.  GEN =
-// false compiles the van der Waals fluid with the energy equation only: the streaming
-// kernels are instantiated both ways, so that the common case carries none of the
-// other laws' code and registers.
+// double well).  The kind is uniform over a launch, so the branches are scalar.  The
+// step kernels are instantiated for the van der Waals fluid with its energy (kLean), for
+// isothermal runs of any law (kIsothermal) and for the Dieterici fluid with its energy
+// (kDieterici), so that the first two carry none of the third's code: its temperature is an
+// out-of-line Newton iteration, around which a kernel spills what it holds.  The others
+// (collision, check, read-back) take any law (kAnyLaw).
 // ---------------------------------------------------------------------------
 enum { kEosVdw = 0, kEosDieterici = 1, kEosWell = 2 };
-template <bool GEN = true, typename PT>
+template <int LAW = kAnyLaw, typename PT>
 __device__ __forceinline__ double eos_p(const PT &P, double rho, double T)
 {
-    if (GEN && P.eos == kEosDieterici) return rho * P.R * T / (1.0 - P.b * rho) * exp(-P.a * rho / (P.R * T));
-    if (GEN && P.eos == kEosWell) {
+    if (LAW == kDieterici || (LAW != kLean && P.eos == kEosDieterici))
+        return rho * P.R * T / (1.0 - P.b * rho) * exp(-P.a * rho / (P.R * T));
+    if (LAW != kLean && P.eos == kEosWell) {
         // p0 + rho E0' - E0 = p0 + beta dl dv (2 rho (dl + dv) - dl dv), dl = rho - rho_l,
         // dv = rho - rho_v, for E0 = beta dl^2 dv^2
         const double dl = rho - P.eos_c[1], dv = rho - P.eos_c[2];
@@ -68,11 +71,11 @@ __device__ __forceinline__ double vdw_p_lean(const PT &P, double rho, double T, 
     return rho * rho * P.R * T * i_rq - P.a * rho * rho;
 }
 // temperature of a streamed state from its internal energy
-template <bool GEN = true, typename PT>
+template <int LAW = kAnyLaw, typename PT>
 __device__ __forceinline__ double eos_T_of_e(const PT &P, double rho, double e)
 {
-    if (GEN && P.isothermal) return P.T0;
-    if (GEN && P.eos == kEosDieterici) return diet_T_of_e(P.a, P.b, P.R, P.Cv, rho, e);
+    if (LAW == kIsothermal || (LAW == kAnyLaw && P.isothermal)) return P.T0;
+    if (LAW == kDieterici || (LAW == kAnyLaw && P.eos == kEosDieterici)) return diet_T_of_e(P.a, P.b, P.R, P.Cv, rho, e);
     return (e + P.a * rho) * P.inv_Cv;
 }
 // temperature of an initial or inflow state given T
@@ -96,11 +99,11 @@ __device__ __forceinline__ double eos_e(const PT &P, double rho, double T)
     return P.Cv * T - (P.eos == kEosVdw ? P.a * rho : 0.0);
 }
 // bit set of the admissibility violations of a state (pressure domain, finiteness)
-template <bool GEN = true, typename PT>
+template <int LAW = kAnyLaw, typename PT>
 __device__ __forceinline__ int eos_bad(const PT &P, double rho, double p)
 {
     if (!isfinite(rho) || !isfinite(p)) return kErrNonfinite;
-    if (!(p > 0.0) || !(rho > 0.0) || !((GEN && P.eos == kEosWell) || 1.0 - P.b * rho > 0.0)) return kErrPressure;
+    if (!(p > 0.0) || !(rho > 0.0) || !((LAW != kLean && LAW != kDieterici && P.eos == kEosWell) || 1.0 - P.b * rho > 0.0)) return kErrPressure;
     return 0;
 }
 

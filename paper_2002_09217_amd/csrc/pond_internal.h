@@ -12,6 +12,8 @@ namespace pond {
 // boundary inside a graph, which longer runs amortise.
 constexpr int kRunPairs = 8;
 enum { kPeriodic = 0, kOutflow = 1, kInflow = 2 };
+// equation-of-state variants of the kernels (pond_device.h)
+enum { kLean = 0, kIsothermal = 1, kDieterici = 2, kAnyLaw = 3 };
 
 // error bits written by the kernels into flags[0]; kErrCollideStage marks an error of
 // the closure that precedes a state's collision (fused step and its check), which makes
@@ -145,9 +147,8 @@ struct LaunchCtx {
     // runtime records at the kernel's own start and end (measurement only)
     hipEvent_t ev_start = nullptr, ev_stop = nullptr;
     int nz = 1;
-    // streaming kernels with the general equation of state (isothermal runs or a
-    // non-van-der-Waals pressure); false: the van der Waals fluid with its energy
-    bool gen_eos = false;
+    // equation-of-state variant of the streaming and fused-step kernels (step_law)
+    int law = kLean;
     // fused step (one kernel per step, the state between steps is the streamed moment
     // planes, mixed FP64/FP32 in the FP32 storage precisions); false: two kernels per
     // step with stored populations
@@ -178,6 +179,8 @@ hipError_t launch_step_double_windows(const LaunchCtx &c, const SlotDesc *slots,
 // fused step: closure of the state in `mom` (every node), raising its errors with
 // kErrCollideStage and counting as a launch; `tiles` as for launch_force_collide
 hipError_t launch_collide_check(const LaunchCtx &c, const SlotDesc *slots, int nslots, int tiles);
+// equation-of-state variant of a configuration's step kernels
+inline int step_law(int dieterici, int isothermal) { return isothermal ? kIsothermal : dieterici ? kDieterici : kLean; }
 // lanes per receiver for a lattice of `tiles` tiles of the current shape: a choice of the
 // lattice alone, so that it runs the same kernel by itself and in a batch
 int step_lanes(const LaunchCtx &c, int tiles);

@@ -78,7 +78,7 @@ hipError_t launch_gather_slot_flags(hipStream_t st, const SlotDesc *slots, int n
 // streaming with the predictor-corrector
 // ---------------------------------------------------------------------------
 // LANES lanes per receiver (step_lanes); the fill uses all lanes of the block
-template <int DIM, int LANES, typename PopT, typename LdsT, int TX, int TY, bool GEN>
+template <int DIM, int LANES, typename PopT, typename LdsT, int TX, int TY, int LAW>
 __global__ void __launch_bounds__(LANES *TX *TY, sizeof(LdsT) == 4 ? 3 : 2)
     k_stream(const SlotDesc *__restrict__ slots, int nslots)
 {
@@ -230,30 +230,33 @@ __global__ void __launch_bounds__(LANES *TX *TY, sizeof(LdsT) == 4 ? 3 : 2)
     double f[Q], g[Q];
     double sUx = Ux, sUy = Uy, sS = 1.0;
     double rho = 0.0;
-    const int err = stream_passes<DIM, LANES, LdsT, LN, LX, NT, GEN>(P, lds, wbase, tid, half, rx, ry, refR0, refR1, refT,
+    const int err = stream_passes<DIM, LANES, LdsT, LN, LX, NT, LAW>(P, lds, wbase, tid, half, rx, ry, refR0, refR1, refT,
                                                                      Ux, Uy, th, Fpx, Fpy, f, g, rho, sUx, sUy, sS);
     store_streamed<DIM, false>(S.mom, N, node, half, f, rho, Ux, Uy, sUx, sUy, sS);
     if (LANES == 1) store_streamed<DIM, false>(S.mom, N, node, 1, g, rho, Ux, Uy, sUx, sUy, sS);
     if (err) raise_error(flags, err, S.parity);
 }
 
-template <int DIM, int LANES, typename PopT, typename LdsT, int TX, int TY, bool GEN>
+template <int DIM, int LANES, typename PopT, typename LdsT, int TX, int TY, int LAW>
 static hipError_t launch_stream_g(const LaunchCtx &c, const SlotDesc *slots, int nslots, int tiles)
 {
     dim3 block(LANES * TX * TY);
     if (c.ev_start)
-        hipExtLaunchKernelGGL((k_stream<DIM, LANES, PopT, LdsT, TX, TY, GEN>), dim3(tiles), block, 0, c.st,
+        hipExtLaunchKernelGGL((k_stream<DIM, LANES, PopT, LdsT, TX, TY, LAW>), dim3(tiles), block, 0, c.st,
                               c.ev_start, c.ev_stop, 0, slots, nslots);
     else
-        hipLaunchKernelGGL((k_stream<DIM, LANES, PopT, LdsT, TX, TY, GEN>), dim3(tiles), block, 0, c.st, slots,
+        hipLaunchKernelGGL((k_stream<DIM, LANES, PopT, LdsT, TX, TY, LAW>), dim3(tiles), block, 0, c.st, slots,
                            nslots);
     return hipGetLastError();
 }
 template <int DIM, int LANES, typename PopT, typename LdsT, int TX, int TY>
 static hipError_t launch_stream_t(const LaunchCtx &c, const SlotDesc *slots, int nslots, int tiles)
 {
-    return c.gen_eos ? launch_stream_g<DIM, LANES, PopT, LdsT, TX, TY, true>(c, slots, nslots, tiles)
-                     : launch_stream_g<DIM, LANES, PopT, LdsT, TX, TY, false>(c, slots, nslots, tiles);
+    switch (c.law) {
+    case kIsothermal: return launch_stream_g<DIM, LANES, PopT, LdsT, TX, TY, kIsothermal>(c, slots, nslots, tiles);
+    case kDieterici: return launch_stream_g<DIM, LANES, PopT, LdsT, TX, TY, kDieterici>(c, slots, nslots, tiles);
+    default: return launch_stream_g<DIM, LANES, PopT, LdsT, TX, TY, kLean>(c, slots, nslots, tiles);
+    }
 }
 template <typename PopT, typename LdsT, int TX, int TY>
 static hipError_t launch_stream_l(const LaunchCtx &c, const SlotDesc *slots, int nslots, int tiles)

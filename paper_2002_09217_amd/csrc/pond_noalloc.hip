@@ -89,7 +89,7 @@ extern "C" int pond_step_noalloc(const pond_config *cfg, void *state0, void *sta
 
     LaunchCtx lc{c.dim, nx, ny, (int)N, c.precision == POND_FP64 ? 0 : (c.precision == POND_FP32_STORE ? 1 : 2),
                  (hipStream_t)c.stream, c.tile < 0 ? 0 : c.tile};
-    lc.gen_eos = c.eos != POND_EOS_VDW || c.isothermal;
+    lc.law = step_law(c.eos == POND_EOS_DIETERICI, c.isothermal);
     int stx, stc, fcx, fcc;
     tile_counts(lc, &stx, &stc, &fcx, &fcc);
     lc.lanes = step_lanes(lc, stc);

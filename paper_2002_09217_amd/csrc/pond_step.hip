@@ -32,7 +32,7 @@
 namespace pond {
 
 // LANES lanes per receiver; the stages before the streaming use all lanes of the block
-template <int DIM, int LANES, bool MIXED, typename LdsT, int TX, int TY, bool GEN>
+template <int DIM, int LANES, bool MIXED, typename LdsT, int TX, int TY, int LAW>
 __global__ void __launch_bounds__(LANES *TX *TY, sizeof(LdsT) == 4 ? 3 : 2)
     k_step(const SlotDesc *__restrict__ slots, int nslots)
 {
@@ -216,7 +216,7 @@ __global__ void __launch_bounds__(LANES *TX *TY, sizeof(LdsT) == 4 ? 3 : 2)
             double Fx = 0.0, Fy = 0.0;
             if (force) korteweg_force<DIM>(s_K, s_K + KN, s_K + 2 * KN, (DIM == 2 ? (hy + 1) * KX : 0) + hx + 1, KX, Fx, Fy);
             const double rho = force ? s_rho[(DIM == 2 ? (hy + 2) * RX : 0) + hx + 2] : pre_c[j][0];
-            err_c |= thermo_state<DIM, GEN>(P, rho, pre_c[j][1], pre_c[j][2], pre_c[j][3], Fx, Fy, visc, s_th, HN, li);
+            err_c |= thermo_state<DIM, LAW>(P, rho, pre_c[j][1], pre_c[j][2], pre_c[j][3], Fx, Fy, visc, s_th, HN, li);
         } else if (cls == kGhost) {
             const POND_GLOBAL GhostFace &G = P.ghost[face];
             s_th[kThQ * HN + li] = flux_potential(P, visc, G.T, G.h);
@@ -336,30 +336,33 @@ __global__ void __launch_bounds__(LANES *TX *TY, sizeof(LdsT) == 4 ? 3 : 2)
     double f[Q], g[Q];
     double sUx = Ux, sUy = Uy, sS = 1.0;
     double rho = 0.0;
-    const int err = stream_passes<DIM, LANES, LdsT, LN, LX, NT, GEN>(P, lds, wbase, tid, half, rx, ry, refR0, refR1, refT,
+    const int err = stream_passes<DIM, LANES, LdsT, LN, LX, NT, LAW>(P, lds, wbase, tid, half, rx, ry, refR0, refR1, refT,
                                                                      Ux, Uy, th, Fpx, Fpy, f, g, rho, sUx, sUy, sS);
     store_streamed<DIM, MIXED>(S.smom_dst, N, node, half, f, rho, Ux, Uy, sUx, sUy, sS);
     if (LANES == 1) store_streamed<DIM, MIXED>(S.smom_dst, N, node, 1, g, rho, Ux, Uy, sUx, sUy, sS);
     if (err) raise_error(flags, err, S.parity);
 }
 
-template <int DIM, int LANES, bool MIXED, typename LdsT, int TX, int TY, bool GEN>
+template <int DIM, int LANES, bool MIXED, typename LdsT, int TX, int TY, int LAW>
 static hipError_t launch_step_g(const LaunchCtx &c, const SlotDesc *slots, int nslots, int tiles)
 {
     dim3 block(LANES * TX * TY);
     if (c.ev_start)
-        hipExtLaunchKernelGGL((k_step<DIM, LANES, MIXED, LdsT, TX, TY, GEN>), dim3(tiles), block, 0, c.st, c.ev_start,
+        hipExtLaunchKernelGGL((k_step<DIM, LANES, MIXED, LdsT, TX, TY, LAW>), dim3(tiles), block, 0, c.st, c.ev_start,
                               c.ev_stop, 0, slots, nslots);
     else
-        hipLaunchKernelGGL((k_step<DIM, LANES, MIXED, LdsT, TX, TY, GEN>), dim3(tiles), block, 0, c.st, slots, nslots);
+        hipLaunchKernelGGL((k_step<DIM, LANES, MIXED, LdsT, TX, TY, LAW>), dim3(tiles), block, 0, c.st, slots, nslots);
     return hipGetLastError();
 }
 
 template <int DIM, int LANES, bool MIXED, typename LdsT, int TX, int TY>
 static hipError_t launch_step_t(const LaunchCtx &c, const SlotDesc *slots, int nslots, int tiles)
 {
-    return c.gen_eos ? launch_step_g<DIM, LANES, MIXED, LdsT, TX, TY, true>(c, slots, nslots, tiles)
-                     : launch_step_g<DIM, LANES, MIXED, LdsT, TX, TY, false>(c, slots, nslots, tiles);
+    switch (c.law) {
+    case kIsothermal: return launch_step_g<DIM, LANES, MIXED, LdsT, TX, TY, kIsothermal>(c, slots, nslots, tiles);
+    case kDieterici: return launch_step_g<DIM, LANES, MIXED, LdsT, TX, TY, kDieterici>(c, slots, nslots, tiles);
+    default: return launch_step_g<DIM, LANES, MIXED, LdsT, TX, TY, kLean>(c, slots, nslots, tiles);
+    }
 }
 
 template <bool MIXED, typename LdsT, int TX, int TY>

@@ -101,6 +101,15 @@ template <int LN> struct PairRow<float, LN> {
     }
 };
 
+// Keeps the arithmetic of a window in front of the closure that uses its results: the
+// compiler would otherwise sink it into the closure's branches, away from its LDS reads
+// (618 registers to scratch in an isothermal kernel).
+template <int N> __device__ __forceinline__ void pin(double (&v)[N])
+{
+#pragma unroll
+    for (int i = 0; i < N; ++i) asm volatile("" : "+v"(v[i]));
+}
+
 // The rows of a lane.  One lane a receiver: fifteen, the five of n = 0, 1, 2.  Two: the five
 // rows of n = 0 (half 1: n = 2), then rows 0..2 (half 1: 2..4) of n = 1, whose middle row
 // both halves take with half its weight.
@@ -307,7 +316,7 @@ __device__ __forceinline__ void window_sums(const T *lds, int node, int half, co
 // centre's gauge).  On return f and g hold the populations in the gauge (sUx, sUy, sS) of the
 // last pass (two lanes a receiver: f those of this half's set, f or g), and (Ux, Uy, th) the
 // gauge it produced; returns the error bits.
-template <int DIM, int LANES, typename LdsT, int LN, int LX, int NT, bool GEN>
+template <int DIM, int LANES, typename LdsT, int LN, int LX, int NT, int LAW>
 __device__ __forceinline__ int stream_passes(const POND_GLOBAL DevParams &P, const LdsT *lds, int node, int tid, int half,
                                              double rx, double ry, double refR0, double refR1, double refT, double &Ux,
                                              double &Uy, double &th, double Fpx, double Fpy,
@@ -326,17 +335,17 @@ __device__ __forceinline__ int stream_passes(const POND_GLOBAL DevParams &P, con
         // long dependent sequence on this hardware); the lean van der Waals closure
         // takes it and 1 / (1 - b rho) from one division
         const double q = 1.0 - P.b * rho;
-        const double i_rq = GEN ? 0.0 : 1.0 / (rho * q);
-        const double i_rho = GEN ? 1.0 / rho : q * i_rq;
+        const double i_rq = LAW != kLean ? 0.0 : 1.0 / (rho * q);
+        const double i_rho = LAW != kLean ? 1.0 / rho : q * i_rq;
         const double E = 0.5 * G2 * i_rho;
         const double ux = jx * i_rho;
         const double uy = DIM == 2 ? jy * i_rho : 0.0;
         const double uhx = ux + 0.5 * Fpx * dt * i_rho;
         const double uhy = DIM == 2 ? uy + 0.5 * Fpy * dt * i_rho : 0.0;
         const double e = E - 0.5 * (uhx * uhx + uhy * uhy);
-        const double T = eos_T_of_e<GEN>(P, rho, e);
-        const double p = GEN ? eos_p<GEN>(P, rho, T) : vdw_p_lean(P, rho, T, i_rq);
-        err |= eos_bad<GEN>(P, rho, p);
+        const double T = eos_T_of_e<LAW>(P, rho, e);
+        const double p = LAW != kLean ? eos_p<LAW>(P, rho, T) : vdw_p_lean(P, rho, T, i_rq);
+        err |= eos_bad<LAW>(P, rho, p);
         sUx = Ux;
         sUy = Uy;
         sS = s;
@@ -360,6 +369,7 @@ __device__ __forceinline__ int stream_passes(const POND_GLOBAL DevParams &P, con
         lagrange_coeffs(Ux - rx, s, A);
         lagrange_coeffs(Uy - ry, s, B);
         window_sums<LANES, LdsT, LN, LX>(lds, node, half, wx, wy, A, B, S);
+        pin(S);
 #pragma unroll
         for (int i = 0; i < 4 && LANES == 2; ++i) S[i] = sum_halves(S[i]);
         // the reference's own sums: R at the velocity (rx, ry)
@@ -382,6 +392,8 @@ __device__ __forceinline__ int stream_passes(const POND_GLOBAL DevParams &P, con
                 window_pops<LANES, true, LdsT, LN, LX>(lds, node, half, wx, wy, Ad, Bd, Uy - ry, s, f, g);
             else
                 window_pops<LANES, false, LdsT, LN, LX>(lds, node, half, wx, wy, Ad, Bd, Uy - ry, s, f, g);
+            pin(f);
+            pin(g);
             // the reference part (see the fill), R a_k b_l, from coefficients computed again
             double ra[3], rb[3];
             if constexpr (kDevI) {

@@ -76,3 +76,16 @@ def test_batch_mixes_lanes_a_receiver(precision):
             assert all(np.array_equal(got[k], ref[k]) for k in ref)
     for lat in lats:
         lat.close()
+
+
+@pytest.mark.parametrize("precision", list(TOL))
+@pytest.mark.parametrize("law", ["isothermal", "double well", "dieterici"])
+def test_laws_with_one_lane_a_receiver(law, precision):
+    """The equation-of-state variants of the one-lane kernels, on 288 tiles."""
+    print(f"law {law} precision {precision}", flush=True)
+    kw = {"isothermal": dict(isothermal=1, T0=1.05 * W.T_CR),
+          "double well": dict(eos=pond.EOS_DOUBLE_WELL, isothermal=1, T0=0.1, eos_c=(8e-4, 5.0, 0.5, 0.1)),
+          "dieterici": dict(eos=pond.EOS_DIETERICI, a=2.0 * W.T_CR / W.RHO_CR, b=0.5 / W.RHO_CR)}[law]
+    rho0 = {"isothermal": 1.5, "double well": 5.0, "dieterici": 2.5}[law]
+    case = W.perturbed(275, 250, seed=9, rho0=rho0, u0=(0.05, -0.02), kappa=0.0176, dt=0.2, **kw)
+    check(run_oracle(case, 2), run_gpu(case, 2, precision, tile=5), ("rho", "ux", "uy", "E", "T", "p"), TOL[precision], law)
