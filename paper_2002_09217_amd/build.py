@@ -25,6 +25,9 @@ HEADERS = ["pond_device.h", "pond_internal.h", "pond_collide.h", "pond_stream.h"
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
+    # kernel arguments preloaded into scalar registers: a wave starts without its first dependent
+    # load (fused step of 256^2 FP64 19.1 -> 18.75 us, of 1000 nodes 5.85 -> 5.76)
+    "-mllvm", "-amdgpu-kernarg-preload-count=16",
     # no packed FP32 instructions in any kernel
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-function", "-Wno-unused-variable",
