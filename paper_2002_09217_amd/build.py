@@ -21,7 +21,7 @@ SOURCES = ["pond_kernels.hip", "pond_step.hip", "pond_kernels3.hip", "pond_api.h
 MAX_ILP = ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]
 UNITS = [(s, MAX_ILP if s == "pond_kernels3.hip" else []) for s in SOURCES] + [
     ("pond_step.hip", ["-DPOND_STEP_DOUBLE_WINDOWS", *MAX_ILP])]
-HEADERS = ["pond_device.h", "pond_internal.h", "pond_collide.h", "pond_stream.h", "pond_eos.h"]
+HEADERS = ["pond_device.h", "pond_internal.h", "pond_collide.h", "pond_stream.h", "pond_eos.h", "pond_readback.h"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

@@ -13,6 +13,7 @@
 #include "pond_eos.h"
 #include "pond_handle.h"
 #include "pond_internal.h"
+#include "pond_readback.h"
 
 using namespace pond;
 
@@ -552,6 +553,7 @@ int pond_create(const pond_config *cfg, pond_handle **out)
         delete h;
         return rc;
     }
+    g_stage.enter();
     *out = h;
     return POND_OK;
 }
@@ -666,11 +668,10 @@ int pond_moments(pond_handle *h, double *rho, double *u, double *T, double *p, d
         size_t off, count;
     } parts[] = {{rho, 0, N}, {u, N, N * dim}, {T, (1 + dim) * N, N}, {p, (2 + dim) * N, N},
                  {E, (3 + dim) * N, N}};
+    ReadBack rb;
     for (auto &pt : parts)
-        if (pt.dst)
-            HIP_TRY(h, hipMemcpyAsync(pt.dst, base + pt.off, sizeof(double) * pt.count,
-                                      hipMemcpyDeviceToHost, h->stream));
-    HIP_TRY(h, hipStreamSynchronize(h->stream));
+        if (pt.dst) rb.add(pt.dst, base + pt.off, pt.count);
+    HIP_TRY(h, rb.run(h->stream));
     return POND_OK;
 }
 
@@ -717,6 +718,7 @@ int pond_destroy(pond_handle *h)
     if (h->stream) (void)hipStreamSynchronize(h->stream);
     free_all(h);
     delete h;
+    g_stage.leave();
     return POND_OK;
 }
 
