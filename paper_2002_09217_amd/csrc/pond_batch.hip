@@ -133,25 +133,86 @@ int rebuild(pond_batch *b)
     return POND_OK;
 }
 
+hipError_t enqueue_group(pond_batch *b, const Group &g, hipStream_t st, int arr)
+{
+    LaunchCtx c{g.dim, 0, 0, 0, g.fp32, st, g.tile};
+    c.law = g.law;
+    c.lanes = g.lanes;
+    c.fused = b->fused;
+    const SlotDesc *d = b->desc_d + (size_t)arr * b->members.size() + g.first;
+    if (b->fused) return launch_step_fused(c, d, g.count, g.st_tiles);
+    const hipError_t e = launch_stream(c, d, g.count, g.st_tiles);
+    return e == hipSuccess ? launch_force_collide(c, d, g.count, g.fc_tiles) : e;
+}
+
 hipError_t enqueue_step(pond_batch *b, hipStream_t st, int arr)
 {
-    const int M = (int)b->members.size();
     for (const Group &g : b->groups) {
-        LaunchCtx c{g.dim, 0, 0, 0, g.fp32, st, g.tile};
-        c.law = g.law;
-        c.lanes = g.lanes;
-        c.fused = b->fused;
-        const SlotDesc *d = b->desc_d + (size_t)arr * M + g.first;
-        hipError_t e;
-        if (b->fused) {
-            e = launch_step_fused(c, d, g.count, g.st_tiles);
-        } else {
-            e = launch_stream(c, d, g.count, g.st_tiles);
-            if (e == hipSuccess) e = launch_force_collide(c, d, g.count, g.fc_tiles);
-        }
+        const hipError_t e = enqueue_group(b, g, st, arr);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
+}
+
+// A long run in branches: no group reads what another writes, so each branch takes some of the
+// groups through all steps of the run, and the launches of a group that leaves the chip idle
+// run beside another's (one after another, the last blocks of each launch drain first).
+// Two jobs each of 64^2, 128^2, 256^2 and 512^2 (three groups), FP32: 135.6 -> 120.5 us a step.
+// A short run stays in one branch: a fork and a join cost about what its three steps gain.
+// At most kBranches of them, the groups spread by their tiles: the process has four hardware
+// queues.
+constexpr int kBranches = 3;
+struct Branches {
+    int n;
+    hipStream_t st[kBranches];
+    int events = 0;
+    hipEvent_t ev[2 * kBranches]; // (live until the capture has ended)
+    explicit Branches(hipStream_t first) : n(1) { st[0] = first; }
+    Branches(const Branches &) = delete;
+    ~Branches()
+    {
+        for (int k = 0; k < events; ++k) (void)hipEventDestroy(ev[k]);
+        for (int k = 1; k < n; ++k) (void)hipStreamDestroy(st[k]);
+    }
+    hipError_t add()
+    {
+        const hipError_t e = hipStreamCreateWithFlags(&st[n], hipStreamNonBlocking);
+        if (e == hipSuccess) ++n;
+        return e;
+    }
+    hipError_t wait(hipStream_t waits, hipStream_t on)
+    {
+        hipError_t e = hipEventCreateWithFlags(&ev[events], hipEventDisableTiming);
+        if (e != hipSuccess) return e;
+        ++events;
+        e = hipEventRecord(ev[events - 1], on);
+        return e == hipSuccess ? hipStreamWaitEvent(waits, ev[events - 1], 0) : e;
+    }
+};
+
+hipError_t enqueue_run(pond_batch *b, Branches &br, int steps, int arr)
+{
+    std::vector<const Group *> by_size;
+    for (const Group &g : b->groups) by_size.push_back(&g);
+    std::stable_sort(by_size.begin(), by_size.end(), [](auto *x, auto *y) { return x->st_tiles > y->st_tiles; });
+    std::vector<const Group *> of[kBranches];
+    long long tiles[kBranches] = {0};
+    for (const Group *g : by_size) {
+        const int k = (int)(std::min_element(tiles, tiles + br.n) - tiles);
+        of[k].push_back(g);
+        tiles[k] += g->st_tiles;
+    }
+    hipError_t e = hipSuccess;
+    for (int k = 1; k < br.n && e == hipSuccess; ++k) e = br.wait(br.st[k], br.st[0]);
+    for (int k = 0; k < br.n; ++k)
+        for (int s = 0; s < steps; ++s)
+            for (const Group *g : of[k])
+                if (e == hipSuccess) e = enqueue_group(b, *g, br.st[k], (arr + s) % b->states());
+    for (int k = 1; k < br.n; ++k) {
+        const hipError_t ej = br.wait(br.st[0], br.st[k]); // (joined also after an error: the capture ends)
+        if (e == hipSuccess) e = ej;
+    }
+    return e;
 }
 
 // fused steps: the closure check of every member's state read by descriptor array `arr`
@@ -173,15 +234,17 @@ bool build_step_graph(pond_batch *b, int kind, int arr)
     hipGraphExec_t &exec = b->step_exec[kind][arr];
     if (exec) return true;
     hipGraph_t g = nullptr;
+    Branches br(b->capture_stream);
+    while (kind == 1 && br.n < std::min(kBranches, (int)b->groups.size()))
+        if (br.add() != hipSuccess) break;
     if (hipStreamBeginCapture(b->capture_stream, hipStreamCaptureModeThreadLocal) != hipSuccess) return false;
-    hipError_t e = hipSuccess;
-    for (int k = 0; k < b->run(kind) && e == hipSuccess; ++k) e = enqueue_step(b, b->capture_stream, (arr + k) % b->states());
+    const hipError_t er = enqueue_run(b, br, b->run(kind), arr);
     const hipError_t ec = hipStreamEndCapture(b->capture_stream, &g);
-    if (e != hipSuccess || ec != hipSuccess || !g) {
+    if (er != hipSuccess || ec != hipSuccess || !g) {
         if (g) (void)hipGraphDestroy(g);
         return false;
     }
-    e = hipGraphInstantiate(&exec, g, nullptr, nullptr, 0);
+    const hipError_t e = hipGraphInstantiate(&exec, g, nullptr, nullptr, 0);
     (void)hipGraphDestroy(g);
     if (e != hipSuccess) {
         exec = nullptr;

@@ -78,6 +78,29 @@ def test_batch_mixes_lanes_a_receiver(precision):
         lat.close()
 
 
+@pytest.mark.parametrize("two_kernel", [0, 1])
+@pytest.mark.parametrize("groups", [1, 2, 3, 5])
+def test_batch_runs_its_groups_side_by_side(groups, two_kernel):
+    """Long runs take the groups in up to three branches, on few and on more groups than that;
+    the members' results are the bits of the same steps alone."""
+    tiles, steps = [2, 5, 2, 5, 0][:groups], 94
+    prec = [pond.FP64, pond.FP64, pond.FP32_STORE, pond.FP32_STORE, pond.FP64][:groups]
+    cases = [W.perturbed(40 + 9 * k, 33, seed=k, kappa=0.0176) for k in range(groups)]
+    print(f"batch of {groups} groups two_kernel {two_kernel}", flush=True)
+    alone = [run_gpu(c, steps, p, tile=t, two_kernel=two_kernel) for c, p, t in zip(cases, prec, tiles)]
+    lats = [pond.Lattice(pond_config(c, p, tile=t, two_kernel=two_kernel)).init_fields(c.rho, c.u, c.T)
+            for c, p, t in zip(cases, prec, tiles)]
+    with pond.Batch() as batch:
+        for lat in lats:
+            batch.add(lat)
+        assert batch.step(steps - 1) == [] and batch.step(1) == []
+        for lat, ref in zip(lats, alone):
+            got = lat.moments()
+            assert all(np.array_equal(got[k], ref[k]) for k in ref)
+    for lat in lats:
+        lat.close()
+
+
 @pytest.mark.parametrize("precision", list(TOL))
 @pytest.mark.parametrize("law", ["isothermal", "double well", "dieterici"])
 def test_laws_with_one_lane_a_receiver(law, precision):
