@@ -6,6 +6,7 @@ the stencil, with a flow fast enough that the stencils of a workgroup do not agr
 Tolerances: FP64 repeats the oracle's sums in another order (1e-12, the parity bound of
 the other FP64 tests), the FP32 forms have the bounds of their box tests: 1e-6 where only
 the stored deviations are rounded, 1e-4 where the window arithmetic is too."""
+import dataclasses
 import functools
 
 import numpy as np
@@ -33,6 +34,33 @@ def test_passes_in_three_dimensions(n, n_pass, precision):
     case = W.perturbed3(*n, seed=5, u0=(0.3, -0.47, 0.2), kappa=0.0176, n_pass=n_pass)
     check(run_oracle3(case, 4), run_gpu(case, 4, precision), ("rho", "ux", "uy", "uz", "E", "T", "p"), TOL[precision],
           case.name)
+
+
+@functools.lru_cache(maxsize=None)
+def cell(kappa):
+    case = W.perturbed3(30, 11, 37, seed=8, u0=(0.2, -0.1, 0.3), kappa=kappa)
+    return case, run_oracle3(case, 2)
+
+
+@pytest.mark.parametrize("kappa", [0.0, 0.0176])
+@pytest.mark.parametrize("copies", [(1, 1), (9, 15), (18, 20)])
+def test_closure_in_chunks_of_planes(copies, kappa):
+    """The closure of a box in blocks of 32 x 8 columns and chunks of 4, 6 and 16 planes (the
+    larger the box the more), ragged in all three, against the oracle on the periodic cell that
+    the box repeats."""
+    kx, ky = copies
+    print(f"closure of {kx} x {ky} cells, kappa {kappa}", flush=True)
+    case, ref = cell(kappa)
+    nx, ny, nz = case.n
+
+    def tiled(f):
+        return np.tile(np.asarray(f).reshape(nz, ny, nx), (1, ky, kx)).ravel()
+
+    box = dataclasses.replace(case, n=(nx * kx, ny * ky, nz), rho=tiled(case.rho), T=tiled(case.T),
+                              u=np.stack([tiled(c) for c in case.u]))
+    got = run_gpu(box, 2, pond.FP64)
+    keys = ("rho", "ux", "uy", "uz", "E", "T", "p")
+    check({k: tiled(ref[k]) for k in keys}, got, keys, TOL[pond.FP64], case.name)
 
 
 @functools.lru_cache(maxsize=None)
