@@ -334,7 +334,8 @@ def main():
     flops = flops_per_node * N
     t_step = kern64["k_step"] * 1e-6
     achieved = flops / t_step / 1e12
-    k_name = "k_step<2, false, double, {tx}, {ty}".format(**kern64["tile"])
+    # (two lanes a receiver: at most one tile a compute unit)
+    k_name = "k_step<2, 2, false, double, {tx}, {ty}".format(**kern64["tile"])
     traffic, traffic_src = traffic_from_profile(k_name, N)
     # the same kernel's mean duration in the committed rocprofv3 kernel trace (same sources)
     dur, dur_src = profile_record("duration", k_name, N)

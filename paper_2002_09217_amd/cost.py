@@ -15,13 +15,16 @@ population storage).  fused_bytes_per_node_step is the floor of a step that kept
 collided populations with their side fields on chip, i.e. one such state read and one
 written (368 B and 256 B).
 
-FLOPs of the streaming kernel (the dominant one), per receiver and pass, for the
-moment-first reconstruction: every set (f, g) has NF moment fields; each field is
+FLOPs of the streaming kernel (the dominant one), per receiver, for the moment-first
+reconstruction.  The last pass: every set (f, g) has NF moment fields; each field is
 interpolated at the departure points of all Q directions with separable cubic weights
 (x: 3 departure abscissae x 5 window rows x 4 taps; y: Q directions x 4 taps) and
-contracted into the Q populations (one multiply and one FMA each).  A FMA counts as
-two flops.  The weights, Lagrange coefficients, moments and EoS of a pass, the donor
-moments of the tile and the output moments are added as fixed terms.
+contracted into the Q populations (one multiply and one FMA each).  The passes before it
+need only the sums rho, J and 2 rho E of the populations, whose weights fold over the
+directions of each axis: 45 FMA in x and 4 in the other axes per row of 15 window values
+of f and g, and 75 FMA per axis to fold.  A FMA counts as two flops.  The weights,
+Lagrange coefficients, moments and EoS of a pass, the donor moments of the tile and the
+output moments are added as fixed terms.
 """
 from __future__ import annotations
 
@@ -94,12 +97,14 @@ def collide_flops_per_node(dim: int) -> int:
 
 
 def stream_flops_per_node(dim: int, n_pass: int) -> int:
+    rows = 15 ** (dim - 1)                              # window rows of the moments: (3 x 5) per further axis
+    sums = 2 * rows * (45 + (4 if dim > 1 else 0)) + 2 * 75 * dim
     if dim == 3:
         # per z-window plane and z power: the D2Q9 x-y contraction of 9 fields (972 FMA
         # with the zero taps) and 27 FMA of the z contraction; 5 planes x 3 powers per set
         per_set_pass = 5 * 3 * (972 + 27)
         fixed_pass = 3 * 16 + 3 * 20 + 81 + 20           # weights, Lagrange coeffs, moments, EoS
-        return n_pass * (2 * per_set_pass * 2 + 2 * fixed_pass) + 2 * 250 + 2 * 250
+        return 2 * per_set_pass * 2 + (n_pass - 1) * sums + n_pass * 2 * fixed_pass + 2 * 250 + 2 * 250
     if dim == 2:
         per_field = 2 * (3 * 5 * 4 + 9 * 4 + 9) + 9   # 2 x 105 FMA + 9 MUL = 219
         fields = 18
@@ -112,4 +117,4 @@ def stream_flops_per_node(dim: int, n_pass: int) -> int:
         fixed_pass = 3 * 16 + 20 + 18 + 20
         donor = 60
         out = 60
-    return n_pass * (fields * per_field + fixed_pass) + donor + out
+    return fields * per_field + (n_pass - 1) * sums + n_pass * fixed_pass + donor + out
