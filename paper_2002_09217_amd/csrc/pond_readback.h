@@ -17,7 +17,7 @@ namespace pond {
 // GB/s: the runtime takes the pages of a fresh array, faulted in one by one, through its own
 // staging on one thread.  Here the DMA goes into pinned pieces, and a few threads move them
 // to the caller's memory, faulting its pages side by side: 2048^2 (201 MB) 6.0 ms instead of
-// 20.9, 1024 x 512 (25 MB) 0.8 instead of 1.5, or 3.6 into pages that the process has not had.
+// 20.9, 1024 x 512 (25 MB) 0.8 instead of 1.5, or 1.5 instead of 3.6 into pages new to the process.
 // Read-backs of one piece go through in one copy, on the calling thread: five copies of a
 // 1000-node lattice took 134 us, one takes 40.  Between the two the runtime's own copies stay:
 // there the gain is at most 0.3 ms, and helpers that meet another pool's spinning threads wait
@@ -107,6 +107,9 @@ struct ReadBack {
         std::atomic<int> failed{(int)hipSuccess};
         int dev = 0;
         hipError_t e = hipGetDevice(&dev);
+        // the fields are written before a helper reads them: the caller's stream may be the
+        // per-thread one, which is another stream in each thread
+        if (e == hipSuccess) e = hipStreamSynchronize(st);
         if (e != hipSuccess) return e;
         auto work = [&](int slot) {
             hipEvent_t done;

@@ -13,9 +13,9 @@ from tests.common import pond_config
 pytestmark = pytest.mark.gpu
 
 
-def lattice(nx, ny, seed):
+def lattice(nx, ny, seed, stream=None):
     case = W.perturbed(nx, ny, seed=seed)
-    return pond.Lattice(pond_config(case, tile=0)).init_fields(case.rho, case.u, case.T)
+    return pond.Lattice(pond_config(case, tile=0, stream=stream)).init_fields(case.rho, case.u, case.T)
 
 
 def read(lat, wanted):
@@ -41,6 +41,15 @@ def test_subsets_of_the_fields_are_the_same_bits(n):
             got = read(lat, wanted)
             assert all(np.array_equal(got[k], one[k]) for k in wanted)
         assert all(np.isfinite(v).all() for v in one.values())
+
+
+def test_pieces_on_the_per_thread_stream():
+    """hipStreamPerThread (handle 2) names another stream in each helper thread: its pieces
+    still hold what the caller's thread computed."""
+    with lattice(1500, 1401, seed=4) as own, lattice(1500, 1401, seed=4, stream=2) as lat:
+        for _ in range(3):
+            ref, got = own.step(2).moments(), lat.step(2).moments()
+            assert all(np.array_equal(got[k], ref[k]) for k in ref)
 
 
 def test_read_backs_side_by_side():
