@@ -140,3 +140,68 @@ def test_laws_with_one_lane_a_receiver(law, precision):
     rho0 = {"isothermal": 1.5, "double well": 5.0, "dieterici": 2.5}[law]
     case = W.perturbed(275, 250, seed=9, rho0=rho0, u0=(0.05, -0.02), kappa=0.0176, dt=0.2, **kw)
     check(run_oracle(case, 2), run_gpu(case, 2, precision, tile=5), ("rho", "ux", "uy", "E", "T", "p"), TOL[precision], law)
+
+
+def assert_crosses(fields, n, axes, block):
+    """In the state that a run ends with, within one block of nodes (so within a tile), some
+    node's u_a is above s = sqrt(theta) and some other's not, and within another below -s and
+    not, for each a of `axes`: stencils then reach the window's first and its last columns, and
+    their neighbours' do not."""
+    grid = tuple(reversed(n))
+    s = np.sqrt(3.0 * fields["p"] / fields["rho"])
+    for a in axes:
+        for sign in (1.0, -1.0):
+            fast = (sign * fields["u" + "xyz"[a]] > s).reshape(grid)
+            blocks = [fast[..., y:y + block[1], x:x + block[0]] for y in range(0, n[1], block[1])
+                      for x in range(0, n[0], block[0])]
+            assert any(b.any() and not b.all() for b in blocks), f"u_{'xyz'[a]} does not cross {sign} s"
+
+
+@functools.lru_cache(maxsize=None)
+def shear3(axes, n_pass):
+    """A box sheared across s and -s in u_x, in u_y or in both, within its tiles of 16 x 8.  The
+    flow is that of shear(): its largest speed, temperature and 3 steps, so its tolerances too."""
+    nx, ny, nz = n = (35, 25, 6)
+    case = W.perturbed3(*n, seed=23, rho0=1.0, t_over_tcr=1.4, kappa=0.0176, n_pass=n_pass, dt=0.2)
+    z, y, x = np.meshgrid(np.arange(nz), np.arange(ny), np.arange(nx), indexing="ij")
+    for a in axes:
+        wave = y / ny if a == 0 else x / nx
+        case.u[a] = (1.2 * np.sin(2.0 * np.pi * wave)).ravel()
+    ref = run_oracle3(case, 3)
+    assert_crosses(ref, n, axes, (16, 8))
+    return case, ref
+
+
+@pytest.mark.parametrize("precision", list(TOL))
+@pytest.mark.parametrize("axes", [(0,), (1,), (0, 1)])
+@pytest.mark.parametrize("n_pass", [1, 2, 3])
+def test_general_window_in_three_dimensions(n_pass, axes, precision):
+    """The window with every tap, which a workgroup takes when one of its stencils reaches
+    the outermost columns or rows."""
+    print(f"3d shear in axes {axes} n_pass {n_pass} precision {precision}", flush=True)
+    case, ref = shear3(axes, n_pass)
+    check(ref, run_gpu(case, 3, precision), ("rho", "ux", "uy", "uz", "E", "T", "p"), TOL[precision], case.name)
+
+
+@functools.lru_cache(maxsize=None)
+def cross_shear(n, n_pass):
+    """shear() turned by a quarter and periodic: u_y crosses s and -s along x."""
+    nx, ny = n
+    case = W.perturbed(nx, ny, seed=24, rho0=1.0, t_over_tcr=1.4, kappa=0.0176, n_pass=n_pass, dt=0.2)
+    case.u[1] = np.tile(1.2 * np.sin(2.0 * np.pi * np.arange(nx) / nx), ny)
+    ref = run_oracle(case, 3)
+    assert_crosses(ref, n, (1,), (16, 8))
+    return case, ref
+
+
+@pytest.mark.parametrize("precision", list(TOL))
+@pytest.mark.parametrize("two_kernel", [0, 1])
+@pytest.mark.parametrize("n,tile", [((250, 275), 0), ((250, 275), 5), ((61, 43), 2), ((61, 43), 5)])
+@pytest.mark.parametrize("n_pass", [1, 2, 3])
+def test_general_window_across_y(n_pass, n, tile, two_kernel, precision):
+    """The outermost rows of the 2D window, whose weights two lanes a receiver split between
+    them: on more tiles than compute units (one lane) and on a few (two)."""
+    print(f"2d shear in u_y {n} n_pass {n_pass} tile {tile} two_kernel {two_kernel} precision {precision}", flush=True)
+    case, ref = cross_shear(n, n_pass)
+    got = run_gpu(case, 3, precision, tile=tile, two_kernel=two_kernel)
+    check(ref, got, ("rho", "ux", "uy", "E", "T", "p"), TOL[precision], case.name)
