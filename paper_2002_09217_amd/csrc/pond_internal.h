@@ -134,6 +134,26 @@ struct DevState {
     void *ring[kFusedRing];
 };
 
+// Makes a stream's device the thread's current one for a scope: events and streams belong to
+// the device that is current when they are made, which need not be that of a handle's stream.
+// (The default and the per-thread stream are those of the current device.)
+struct StreamDevice {
+    int before = 0, device = 0;
+    hipError_t status;
+    explicit StreamDevice(hipStream_t st) : status(hipGetDevice(&before))
+    {
+        device = before;
+        if (status == hipSuccess && st && st != hipStreamLegacy && st != hipStreamPerThread)
+            status = hipStreamGetDevice(st, &device);
+        if (status == hipSuccess && device != before) status = hipSetDevice(device);
+    }
+    ~StreamDevice()
+    {
+        if (device != before) (void)hipSetDevice(before);
+    }
+    StreamDevice(const StreamDevice &) = delete;
+};
+
 // ---------------------------------------------------------------------------
 // launchers (pond_kernels.hip); all enqueue on `st` and return hipError_t
 // ---------------------------------------------------------------------------

@@ -10,6 +10,8 @@
 #include <mutex>
 #include <thread>
 
+#include "pond_internal.h"
+
 namespace pond {
 
 // ---------------------------------------------------------------------------
@@ -105,15 +107,15 @@ struct ReadBack {
         const size_t n = first[parts];
         std::atomic<size_t> next{0};
         std::atomic<int> failed{(int)hipSuccess};
-        int dev = 0;
-        hipError_t e = hipGetDevice(&dev);
+        const StreamDevice on(st);
+        hipError_t e = on.status;
         // the fields are written before a helper reads them: the caller's stream may be the
         // per-thread one, which is another stream in each thread
         if (e == hipSuccess) e = hipStreamSynchronize(st);
         if (e != hipSuccess) return e;
         auto work = [&](int slot) {
             hipEvent_t done;
-            hipError_t r = hipSetDevice(dev);
+            hipError_t r = hipSetDevice(on.device);
             if (r == hipSuccess) r = hipEventCreateWithFlags(&done, hipEventDisableTiming);
             if (r != hipSuccess) {
                 failed = (int)r;

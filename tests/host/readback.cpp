@@ -1,0 +1,81 @@
+// Read-backs on the two-device runtime of this folder; exits with the line of the first check
+// that fails, modulo 256.
+#include <cstdio>
+#include <string>
+#include <vector>
+
+#include "pond_readback.h"
+
+using namespace pond;
+
+#define CHECK(x)                                               \
+    do {                                                       \
+        if (!(x)) {                                            \
+            std::printf("line %d: %s\n", __LINE__, #x);        \
+            std::exit(__LINE__ % 256 ? __LINE__ % 256 : 1);    \
+        }                                                      \
+    } while (0)
+
+static hipStream_t stream_on(int device)
+{
+    hipStream_t s;
+    fake::device = device;
+    CHECK(hipStreamCreateWithFlags(&s, hipStreamNonBlocking) == hipSuccess);
+    fake::device = 0;
+    return s;
+}
+
+// five fields of n doubles from the "device" into `dst`, of which those not NULL are read
+static void read(size_t n, hipStream_t st, std::vector<double *> dst, hipError_t want = hipSuccess)
+{
+    std::vector<double> src(5 * n);
+    for (size_t i = 0; i < src.size(); ++i) src[i] = 0.5 + (double)i;
+    const int before = fake::device;
+    fake::copies.clear();
+    ReadBack rb;
+    for (int i = 0; i < 5; ++i)
+        if (dst[i]) rb.add(dst[i], src.data() + i * n, n);
+    CHECK(rb.run(st) == want);
+    CHECK(fake::device == before); // the caller's current device is its own
+    for (int i = 0; i < 5 && want == hipSuccess; ++i)
+        for (size_t k = 0; dst[i] && k < n; ++k) CHECK(dst[i][k] == src[i * n + k]);
+}
+
+struct Arrays {
+    std::vector<std::vector<double>> a;
+    explicit Arrays(size_t n) : a(5, std::vector<double>(n, -1.0)) {}
+    std::vector<double *> all()
+    {
+        std::vector<double *> p;
+        for (auto &v : a) p.push_back(v.data());
+        return p;
+    }
+};
+
+constexpr size_t kSmall = 1000, kMiddle = 200000, kLarge = 700001; // one piece, runtime copies, pieces
+
+// a stream of a device that is not the caller's current one
+static void device()
+{
+    for (size_t n : {kSmall, kMiddle, kLarge})
+        for (int current : {0, 1}) {
+            hipStream_t st = stream_on(1 - current);
+            fake::device = current;
+            read(n, st, Arrays(n).all());
+            read(n, hipStreamPerThread, Arrays(n).all());
+            hipStreamDestroy(st);
+        }
+    CHECK(fake::events == 0);
+}
+
+int main(int, char **argv)
+{
+    const std::string what = argv[1];
+    g_stage.enter();
+    if (what == "device") device();
+    else return 255;
+    CHECK(!fake::pinned.empty());
+    g_stage.leave();
+    CHECK(fake::pinned.empty() && fake::streams == 0);
+    return 0;
+}
