@@ -68,11 +68,24 @@ static void device()
     CHECK(fake::events == 0);
 }
 
+// a helper that cannot have what it needs leaves its pieces to the others
+static void events()
+{
+    hipStream_t st = stream_on(0);
+    for (int left : {3, 1, 0}) {
+        fake::events_left = left;
+        read(kLarge, st, Arrays(kLarge).all());
+        CHECK(fake::events == 0);
+    }
+    hipStreamDestroy(st);
+}
+
 int main(int, char **argv)
 {
     const std::string what = argv[1];
     g_stage.enter();
     if (what == "device") device();
+    else if (what == "events") events();
     else return 255;
     CHECK(!fake::pinned.empty());
     g_stage.leave();
