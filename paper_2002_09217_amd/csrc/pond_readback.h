@@ -64,10 +64,14 @@ struct ReadBack {
     } part[kMost];
     int parts = 0;
     size_t total = 0;
+    void add(const Part &p)
+    {
+        part[parts++] = p;
+        total += p.bytes;
+    }
     void add(double *dst, const double *src, size_t count)
     {
-        part[parts++] = Part{(char *)dst, (const char *)src, count * sizeof(double)};
-        total += count * sizeof(double);
+        add(Part{(char *)dst, (const char *)src, count * sizeof(double)});
     }
     hipError_t direct(hipStream_t st) const
     {
@@ -153,10 +157,26 @@ struct ReadBack {
         for (int t = 0; t < slots; ++t) (void)hipEventDestroy(done[t]);
         return (hipError_t)failed.load();
     }
+    static bool page_locked(const void *p)
+    {
+        hipPointerAttribute_t a;
+        if (hipPointerGetAttributes(&a, p) == hipSuccess) return a.type != hipMemoryTypeUnregistered;
+        (void)hipGetLastError();
+        return false;
+    }
     // ends with the copies done (the stream's earlier work included)
     hipError_t run(hipStream_t st) const
     {
         if (total > kPieceBytes && total <= kStageBytes) return direct(st);
+        if (total > kStageBytes) {
+            // page-locked arrays take the DMA themselves (2048^2: 4.0 ms, 5.4 through the pieces)
+            ReadBack locked, paged;
+            for (int i = 0; i < parts; ++i) (page_locked(part[i].dst) ? locked : paged).add(part[i]);
+            if (locked.parts) {
+                const hipError_t e = locked.direct(st);
+                return e != hipSuccess || !paged.parts ? e : paged.run(st);
+            }
+        }
         std::unique_lock<std::mutex> l(g_stage.in_use, std::try_to_lock);
         if (l.owns_lock() && !g_stage.buf) {
             void *p = nullptr;

@@ -80,12 +80,38 @@ static void events()
     hipStreamDestroy(st);
 }
 
+// page-locked arrays are copied into directly, the others beside them through the staging
+static void locked()
+{
+    hipStream_t st = stream_on(0);
+    double *pin = nullptr;
+    CHECK(hipHostMalloc((void **)&pin, 3 * kLarge * sizeof(double), hipHostMallocDefault) == hipSuccess);
+    Arrays other(kLarge);
+    auto copied_whole = [](const double *dst) {
+        for (const auto &c : fake::copies)
+            if (c.dst == (const char *)dst) return c.bytes == kLarge * sizeof(double);
+        return false;
+    };
+    std::vector<double *> dst = other.all();
+    dst[1] = pin, dst[3] = pin + kLarge;
+    read(kLarge, st, dst); // three fields of pageable memory are above the staging still
+    CHECK(copied_whole(dst[1]) && copied_whole(dst[3]) && !copied_whole(dst[0]));
+    dst[0] = pin + 2 * kLarge;
+    read(kLarge, st, dst); // two are within it: the runtime's copies
+    for (double *d : dst) CHECK(copied_whole(d));
+    read(kLarge, st, {pin, pin + kLarge, pin + 2 * kLarge, nullptr, nullptr});
+    CHECK(fake::copies.size() == 3);
+    hipHostFree(pin);
+    hipStreamDestroy(st);
+}
+
 int main(int, char **argv)
 {
     const std::string what = argv[1];
     g_stage.enter();
     if (what == "device") device();
     else if (what == "events") events();
+    else if (what == "locked") locked();
     else return 255;
     CHECK(!fake::pinned.empty());
     g_stage.leave();
