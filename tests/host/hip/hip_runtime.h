@@ -49,14 +49,14 @@ struct Copy {
 };
 inline std::recursive_mutex lock;
 inline std::vector<Copy> copies;          // every hipMemcpyAsync
-inline std::map<const char *, size_t> pinned; // live hipHostMalloc allocations
+inline std::map<const char *, size_t> pinned, on_device; // live hipHostMalloc and hipMalloc allocations
 inline int streams = 0, events = 0, captures = 0, events_left = 1 << 30, streams_left = 1 << 30;
 inline int device_of(hipStream_t s) { return (size_t)s <= 2 ? device : s->device; }
-inline bool is_pinned(const void *p)
+inline bool within(const std::map<const char *, size_t> &blocks, const void *p)
 {
     std::lock_guard<std::recursive_mutex> l(lock);
-    auto it = pinned.upper_bound((const char *)p);
-    return it != pinned.begin() && (const char *)p < (--it)->first + it->second;
+    auto it = blocks.upper_bound((const char *)p);
+    return it != blocks.begin() && (const char *)p < (--it)->first + it->second;
 }
 } // namespace fake
 
@@ -118,8 +118,20 @@ inline hipError_t hipMemcpyAsync(void *dst, const void *src, size_t n, hipMemcpy
     return hipSuccess;
 }
 inline hipError_t hipMemcpy(void *dst, const void *src, size_t n, hipMemcpyKind) { return std::memcpy(dst, src, n), hipSuccess; }
-inline hipError_t hipMalloc(void **p, size_t n) { return *p = std::malloc(n), hipSuccess; }
-inline hipError_t hipFree(void *p) { return std::free(p), hipSuccess; }
+inline hipError_t hipMalloc(void **p, size_t n)
+{
+    std::lock_guard<std::recursive_mutex> l(fake::lock);
+    *p = std::malloc(n);
+    fake::on_device[(const char *)*p] = n;
+    return hipSuccess;
+}
+inline hipError_t hipFree(void *p)
+{
+    std::lock_guard<std::recursive_mutex> l(fake::lock);
+    fake::on_device.erase((const char *)p);
+    std::free(p);
+    return hipSuccess;
+}
 inline hipError_t hipHostMalloc(void **p, size_t n, unsigned)
 {
     std::lock_guard<std::recursive_mutex> l(fake::lock);
@@ -136,7 +148,10 @@ inline hipError_t hipHostFree(void *p)
 }
 inline hipError_t hipPointerGetAttributes(hipPointerAttribute_t *a, const void *p)
 {
-    return a->type = fake::is_pinned(p) ? hipMemoryTypeHost : hipMemoryTypeUnregistered, hipSuccess;
+    a->type = fake::within(fake::pinned, p)      ? hipMemoryTypeHost
+              : fake::within(fake::on_device, p) ? hipMemoryTypeDevice
+                                                 : hipMemoryTypeUnregistered;
+    return hipSuccess;
 }
 inline hipError_t hipStreamBeginCapture(hipStream_t s, hipStreamCaptureMode)
 {

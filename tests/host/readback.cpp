@@ -80,6 +80,25 @@ static void events()
     hipStreamDestroy(st);
 }
 
+// device arrays, which the runtime's copies take too, are not written by the host
+static void on_device()
+{
+    hipStream_t st = stream_on(0);
+    double *dev = nullptr;
+    CHECK(hipMalloc((void **)&dev, kLarge * sizeof(double)) == hipSuccess);
+    for (size_t n : {kSmall, kMiddle, kLarge}) {
+        Arrays host(n);
+        std::vector<double *> dst = host.all();
+        dst[2] = dev;
+        read(n, st, dst);
+        bool copied = false;
+        for (const auto &c : fake::copies) copied = copied || (c.dst == (const char *)dev && c.bytes == n * sizeof(double));
+        CHECK(copied);
+    }
+    hipFree(dev);
+    hipStreamDestroy(st);
+}
+
 // page-locked arrays are copied into directly, the others beside them through the staging
 static void locked()
 {
@@ -112,6 +131,7 @@ int main(int, char **argv)
     if (what == "device") device();
     else if (what == "events") events();
     else if (what == "locked") locked();
+    else if (what == "on_device") on_device();
     else return 255;
     CHECK(!fake::pinned.empty());
     g_stage.leave();

@@ -31,6 +31,6 @@ def run(*cmd, **kw):
     assert r.returncode == 0, f"{cmd[1:]}: {r.returncode} {r.stdout}{r.stderr}"
 
 
-@pytest.mark.parametrize("what", ["device", "events", "locked"])
+@pytest.mark.parametrize("what", ["device", "events", "locked", "on_device"])
 def test_read_back(program, what):
     run(program("readback"), what)
