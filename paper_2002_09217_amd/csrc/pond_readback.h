@@ -3,6 +3,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <sched.h>
 
 #include <algorithm>
 #include <atomic>
@@ -164,6 +165,13 @@ struct ReadBack {
         (void)hipGetLastError();
         return hipMemoryTypeUnregistered;
     }
+    // cores that the calling thread, and so its helpers, may run on
+    static int cores()
+    {
+        cpu_set_t set;
+        if (sched_getaffinity(0, sizeof set, &set) == 0) return CPU_COUNT(&set);
+        return std::max(1, (int)std::thread::hardware_concurrency());
+    }
     // ends with the copies done (the stream's earlier work included)
     hipError_t run(hipStream_t st) const
     {
@@ -177,6 +185,9 @@ struct ReadBack {
                 const hipError_t e = locked.direct(st);
                 return e != hipSuccess || !paged.parts ? e : paged.run(st);
             }
+            // on one core helpers only take turns (1024^2 4.9 ms, 4.75 by the runtime; on two
+            // 2.9 against 4.76)
+            if (cores() == 1) return direct(st);
         } else {
             // an array on the device is none that the host may write (0.3 us a query)
             for (int i = 0; i < parts; ++i)

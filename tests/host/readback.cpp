@@ -124,6 +124,15 @@ static void locked()
     hipStreamDestroy(st);
 }
 
+// a process of one core has no helper: the runtime's copies, not one piece after another
+static void one_core()
+{
+    hipStream_t st = stream_on(0);
+    read(kLarge, st, Arrays(kLarge).all());
+    CHECK(fake::copies.size() == 5);
+    hipStreamDestroy(st);
+}
+
 int main(int, char **argv)
 {
     const std::string what = argv[1];
@@ -132,6 +141,7 @@ int main(int, char **argv)
     else if (what == "events") events();
     else if (what == "locked") locked();
     else if (what == "on_device") on_device();
+    else if (what == "one_core") return one_core(), 0;
     else return 255;
     CHECK(!fake::pinned.empty());
     g_stage.leave();

@@ -34,3 +34,7 @@ def run(*cmd, **kw):
 @pytest.mark.parametrize("what", ["device", "events", "locked", "on_device"])
 def test_read_back(program, what):
     run(program("readback"), what)
+
+
+def test_read_back_on_one_core(program):
+    run(program("readback"), "one_core", preexec_fn=lambda: os.sched_setaffinity(0, sorted(os.sched_getaffinity(0))[:1]))
