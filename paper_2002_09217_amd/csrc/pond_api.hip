@@ -661,8 +661,7 @@ int pond_moments(pond_handle *h, double *rho, double *u, double *T, double *p, d
     int buf = 0;
     int rc = readback_state(h, &buf);
     if (rc != POND_OK) return rc;
-    HIP_TRY(h, launch_macro(h->lc, h->ds, buf, h->ds.aux));
-    const double *base = h->ds.aux;
+    double *const base = h->ds.aux;
     struct {
         double *dst;
         size_t off, count;
@@ -671,7 +670,7 @@ int pond_moments(pond_handle *h, double *rho, double *u, double *T, double *p, d
     ReadBack rb;
     for (auto &pt : parts)
         if (pt.dst) rb.add(pt.dst, base + pt.off, pt.count);
-    HIP_TRY(h, rb.run(h->stream));
+    HIP_TRY(h, rb.run(h->stream, base, (4 + dim) * N, [&](double *out) { return launch_macro(h->lc, h->ds, buf, out); }));
     return POND_OK;
 }
 

@@ -21,8 +21,11 @@ namespace pond {
 // staging on one thread.  Here the DMA goes into pinned pieces, and a few threads move them
 // to the caller's memory, faulting its pages side by side: 2048^2 (201 MB) 6.0 ms instead of
 // 20.9, 1024 x 512 (25 MB) 0.8 instead of 1.5, or 1.5 instead of 3.6 into pages new to the process.
-// Read-backs of one piece go through in one copy, on the calling thread: five copies of a
-// 1000-node lattice took 134 us, one takes 40.  Between the two the runtime's own copies stay:
+// Where all fields fit a piece the kernel that forms them writes them there (hipHostMalloc'ed
+// memory is the device's too): five copies of a 1000-node lattice took 134 us.  A copy into
+// the piece would be as fast, but the first one above 16 KiB starts a copy engine, 6 ms that
+// a process of such lattices does not pay otherwise.  Parts of more fields that fit a piece
+// take one copy.  Between the sizes the runtime's own copies stay:
 // there the gain is at most 0.3 ms, and helpers that meet another pool's spinning threads wait
 // milliseconds for a core (512^2 right after a conversion on all 16 cores: 0.8 ms by the
 // runtime, 1.2 with one helper, 2.1 with three, 3.8 with five).
@@ -172,35 +175,49 @@ struct ReadBack {
         if (sched_getaffinity(0, sizeof set, &set) == 0) return CPU_COUNT(&set);
         return std::max(1, (int)std::thread::hardware_concurrency());
     }
-    // ends with the copies done (the stream's earlier work included)
-    hipError_t run(hipStream_t st) const
+    // Reads back the added parts of the `whole` doubles that `write` (an address, to which it
+    // enqueues the kernel that forms them) leaves at `dev`; ends with the copies done, the
+    // stream's earlier work included.
+    template <typename Write> hipError_t run(hipStream_t st, double *dev, size_t whole, Write write) const
     {
-        if (total > kPieceBytes && total <= kStageBytes) return direct(st);
+        hipError_t e;
+        std::unique_lock<std::mutex> l(g_stage.in_use, std::defer_lock);
+        // an array on the device is none that the host may write (0.3 us a query)
+        bool host = true;
+        for (int i = 0; i < parts && total <= kPieceBytes; ++i)
+            host = host && memory_of(part[i].dst) != hipMemoryTypeDevice;
+        if (whole * sizeof(double) <= kPieceBytes && host && staging(l)) {
+            if ((e = write((double *)g_stage.buf)) != hipSuccess || (e = hipStreamSynchronize(st)) != hipSuccess) return e;
+            for (int i = 0; i < parts; ++i)
+                std::memcpy(part[i].dst, g_stage.buf + (part[i].src - (const char *)dev), part[i].bytes);
+            return hipSuccess;
+        }
+        if ((e = write(dev)) != hipSuccess) return e;
+        if (!host || (total > kPieceBytes && total <= kStageBytes)) return direct(st);
         if (total > kStageBytes) {
             // page-locked arrays take the DMA themselves (2048^2: 4.0 ms, 5.4 through the pieces)
             ReadBack locked, paged;
             for (int i = 0; i < parts; ++i)
                 (memory_of(part[i].dst) != hipMemoryTypeUnregistered ? locked : paged).add(part[i]);
-            if (locked.parts) {
-                const hipError_t e = locked.direct(st);
-                return e != hipSuccess || !paged.parts ? e : paged.run(st);
-            }
+            if (locked.parts && (e = locked.direct(st)) != hipSuccess) return e;
             // on one core helpers only take turns (1024^2 4.9 ms, 4.75 by the runtime; on two
             // 2.9 against 4.76)
-            if (cores() == 1) return direct(st);
-        } else {
-            // an array on the device is none that the host may write (0.3 us a query)
-            for (int i = 0; i < parts; ++i)
-                if (memory_of(part[i].dst) == hipMemoryTypeDevice) return direct(st);
+            if (paged.total <= kStageBytes || cores() == 1 || !staging(l)) return paged.direct(st);
+            return paged.pieces(st, g_stage.buf);
         }
-        std::unique_lock<std::mutex> l(g_stage.in_use, std::try_to_lock);
-        if (l.owns_lock() && !g_stage.buf) {
-            void *p = nullptr;
-            if (hipHostMalloc(&p, kStageBytes, hipHostMallocPortable) == hipSuccess) g_stage.buf = (char *)p;
-            else (void)hipGetLastError();
-        }
-        if (!l.owns_lock() || !g_stage.buf) return direct(st);
-        return total <= kPieceBytes ? single(st, g_stage.buf) : pieces(st, g_stage.buf);
+        return staging(l) ? single(st, g_stage.buf) : direct(st);
+    }
+
+private:
+    // takes the staging, unless another read-back has it or there is none to be had
+    static bool staging(std::unique_lock<std::mutex> &l)
+    {
+        if (!l.owns_lock() && !l.try_lock()) return false;
+        if (g_stage.buf) return true;
+        void *p = nullptr;
+        if (hipHostMalloc(&p, kStageBytes, hipHostMallocPortable) == hipSuccess) g_stage.buf = (char *)p;
+        else (void)hipGetLastError();
+        return g_stage.buf != nullptr;
     }
 };
 

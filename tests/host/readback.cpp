@@ -29,16 +29,19 @@ static hipStream_t stream_on(int device)
 static void read(size_t n, hipStream_t st, std::vector<double *> dst, hipError_t want = hipSuccess)
 {
     std::vector<double> src(5 * n);
-    for (size_t i = 0; i < src.size(); ++i) src[i] = 0.5 + (double)i;
+    auto form = [&](double *out) {
+        for (size_t i = 0; i < src.size(); ++i) out[i] = 0.5 + (double)i;
+        return hipSuccess;
+    };
     const int before = fake::device;
     fake::copies.clear();
     ReadBack rb;
     for (int i = 0; i < 5; ++i)
         if (dst[i]) rb.add(dst[i], src.data() + i * n, n);
-    CHECK(rb.run(st) == want);
+    CHECK(rb.run(st, src.data(), src.size(), form) == want);
     CHECK(fake::device == before); // the caller's current device is its own
     for (int i = 0; i < 5 && want == hipSuccess; ++i)
-        for (size_t k = 0; dst[i] && k < n; ++k) CHECK(dst[i][k] == src[i * n + k]);
+        for (size_t k = 0; dst[i] && k < n; ++k) CHECK(dst[i][k] == 0.5 + (double)(i * n + k));
 }
 
 struct Arrays {
@@ -124,6 +127,20 @@ static void locked()
     hipStreamDestroy(st);
 }
 
+// all fields of a small lattice are formed in the staging: no copy
+static void small()
+{
+    hipStream_t st = stream_on(0);
+    Arrays a(kSmall), b(100000);
+    read(kSmall, st, a.all());
+    CHECK(fake::copies.empty());
+    read(kSmall, st, {a.all()[0], nullptr, nullptr, a.all()[3], nullptr});
+    CHECK(fake::copies.empty());
+    read(100000, st, {nullptr, b.all()[1], b.all()[2], nullptr, nullptr}); // two of a larger one: one copy
+    CHECK(fake::copies.size() == 1 && fake::within(fake::pinned, fake::copies[0].dst));
+    hipStreamDestroy(st);
+}
+
 // a process of one core has no helper: the runtime's copies, not one piece after another
 static void one_core()
 {
@@ -141,6 +158,7 @@ int main(int, char **argv)
     else if (what == "events") events();
     else if (what == "locked") locked();
     else if (what == "on_device") on_device();
+    else if (what == "small") small();
     else if (what == "one_core") return one_core(), 0;
     else return 255;
     CHECK(!fake::pinned.empty());

@@ -31,7 +31,7 @@ def run(*cmd, **kw):
     assert r.returncode == 0, f"{cmd[1:]}: {r.returncode} {r.stdout}{r.stderr}"
 
 
-@pytest.mark.parametrize("what", ["device", "events", "locked", "on_device"])
+@pytest.mark.parametrize("what", ["device", "events", "locked", "on_device", "small"])
 def test_read_back(program, what):
     run(program("readback"), what)
 
