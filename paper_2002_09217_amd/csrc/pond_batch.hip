@@ -30,6 +30,9 @@ namespace {
 // largest tile count of one launch: keeps blocks x threads per block below 2^31
 constexpr long long kMaxLaunchTiles = 1LL << 21;
 
+// most branches of a captured run: the process has four hardware queues
+constexpr int kBranches = 3;
+
 struct Group {
     int dim, fp32, tile;
     int law;                 // equation-of-state variant of the step kernels
@@ -44,6 +47,7 @@ struct pond_batch {
     hipStream_t stream = nullptr;
     bool own_stream = false;
     hipStream_t capture_stream = nullptr;
+    hipStream_t branch[kBranches - 1] = {}; // streams beside it in long runs, made when first needed
     std::vector<pond_handle *> members;  // order of addition
     // built from the members on demand
     bool dirty = true;
@@ -159,26 +163,30 @@ hipError_t enqueue_step(pond_batch *b, hipStream_t st, int arr)
 // run beside another's (one after another, the last blocks of each launch drain first).
 // Two jobs each of 64^2, 128^2, 256^2 and 512^2 (three groups), FP32: 135.6 -> 120.5 us a step.
 // A short run stays in one branch: a fork and a join cost about what its three steps gain.
-// At most kBranches of them, the groups spread by their tiles: the process has four hardware
-// queues.
-constexpr int kBranches = 3;
+// At most kBranches of them, the groups spread by their tiles.
 struct Branches {
-    int n;
+    int n = 1;
     hipStream_t st[kBranches];
     int events = 0;
     hipEvent_t ev[2 * kBranches]; // (live until the capture has ended)
-    explicit Branches(hipStream_t first) : n(1) { st[0] = first; }
+    // at most `most` of them, fewer where a stream cannot be had; the streams stay with the batch
+    Branches(pond_batch *b, int most)
+    {
+        st[0] = b->capture_stream;
+        for (; n < most; ++n) {
+            hipStream_t &s = b->branch[n - 1];
+            if (!s && hipStreamCreateWithFlags(&s, hipStreamNonBlocking) != hipSuccess) {
+                s = nullptr;
+                (void)hipGetLastError();
+                break;
+            }
+            st[n] = s;
+        }
+    }
     Branches(const Branches &) = delete;
     ~Branches()
     {
         for (int k = 0; k < events; ++k) (void)hipEventDestroy(ev[k]);
-        for (int k = 1; k < n; ++k) (void)hipStreamDestroy(st[k]);
-    }
-    hipError_t add()
-    {
-        const hipError_t e = hipStreamCreateWithFlags(&st[n], hipStreamNonBlocking);
-        if (e == hipSuccess) ++n;
-        return e;
     }
     hipError_t wait(hipStream_t waits, hipStream_t on)
     {
@@ -234,9 +242,9 @@ bool build_step_graph(pond_batch *b, int kind, int arr)
     hipGraphExec_t &exec = b->step_exec[kind][arr];
     if (exec) return true;
     hipGraph_t g = nullptr;
-    Branches br(b->capture_stream);
-    while (kind == 1 && br.n < std::min(kBranches, (int)b->groups.size()))
-        if (br.add() != hipSuccess) break;
+    // the branches' streams and events are the batch's device's, whichever is current now
+    const StreamDevice on(b->capture_stream);
+    Branches br(b, kind == 1 && on.status == hipSuccess ? std::min(kBranches, (int)b->groups.size()) : 1);
     if (hipStreamBeginCapture(b->capture_stream, hipStreamCaptureModeThreadLocal) != hipSuccess) return false;
     const hipError_t er = enqueue_run(b, br, b->run(kind), arr);
     const hipError_t ec = hipStreamEndCapture(b->capture_stream, &g);
@@ -403,6 +411,8 @@ int pond_batch_destroy(pond_batch *b)
     if (b->desc_d) (void)hipFree(b->desc_d);
     if (b->flags_d) (void)hipFree(b->flags_d);
     if (b->capture_stream) (void)hipStreamDestroy(b->capture_stream);
+    for (hipStream_t s : b->branch)
+        if (s) (void)hipStreamDestroy(s);
     if (b->own_stream && b->stream) (void)hipStreamDestroy(b->stream);
     delete b;
     return POND_OK;

@@ -1,0 +1,107 @@
+// Batches on the two-device runtime of this folder: the library's scheduler with launchers that
+// only note where they were sent.  Exits with the line of the first check that fails, modulo 256.
+#include <cstdio>
+#include <memory>
+#include <new>
+#include <string>
+
+#include "pond_handle.h"
+
+using namespace pond;
+
+#define CHECK(x)                                               \
+    do {                                                       \
+        if (!(x)) {                                            \
+            std::printf("line %d: %s\n", __LINE__, #x);        \
+            std::exit(__LINE__ % 256 ? __LINE__ % 256 : 1);    \
+        }                                                      \
+    } while (0)
+
+static int launches, elsewhere, branches_used;
+static hipStream_t seen[8];
+static hipError_t launched(const LaunchCtx &c)
+{
+    ++launches;
+    if (fake::device_of(c.st) != 0) ++elsewhere; // the members' memory is on device 0
+    int k = 0;
+    while (k < branches_used && seen[k] != c.st) ++k;
+    if (k == branches_used && k < 8) seen[branches_used++] = c.st;
+    return hipSuccess;
+}
+namespace pond {
+hipError_t launch_stream(const LaunchCtx &c, const SlotDesc *, int, int) { return launched(c); }
+hipError_t launch_force_collide(const LaunchCtx &c, const SlotDesc *, int, int) { return launched(c); }
+hipError_t launch_step_fused(const LaunchCtx &c, const SlotDesc *, int, int) { return launched(c); }
+hipError_t launch_collide_check(const LaunchCtx &, const SlotDesc *, int, int) { return hipSuccess; }
+hipError_t launch_reset_slot_flags(hipStream_t, const SlotDesc *, int) { return hipSuccess; }
+hipError_t launch_gather_slot_flags(hipStream_t, const SlotDesc *, int, int *) { return hipSuccess; }
+int handle_fail(pond_handle *, int code, const char *, ...) { return code; }
+int handle_finish_batch(pond_handle *h, const int *, int nsteps) { return h->steps += nsteps, POND_OK; }
+} // namespace pond
+
+// a member of its own group
+static std::unique_ptr<pond_handle> member(int tile, bool fused)
+{
+    std::unique_ptr<pond_handle> h(new pond_handle());
+    h->lc = LaunchCtx{2, 64, 64, 4096, 0, nullptr, tile};
+    h->lc.fused = fused;
+    h->initialised = true;
+    h->st_tiles = h->fc_tiles = 16 * (1 + tile);
+    return h;
+}
+
+// a batch on device 0 of `groups` groups, stepped while `current` is the current device
+static void step(int groups, bool fused, int current, int want_branches)
+{
+    const int streams = fake::streams, events = fake::events;
+    pond_batch *b = nullptr;
+    fake::device = 0;
+    CHECK(pond_batch_create(nullptr, &b) == POND_OK);
+    std::unique_ptr<pond_handle> h[6];
+    for (int i = 0; i < groups; ++i) {
+        h[i] = member(i, fused);
+        CHECK(pond_batch_add(b, h[i].get()) == POND_OK);
+    }
+    fake::device = current;
+    const int run = fused ? kFusedRun : 2 * kRunPairs;
+    for (int change = 0; change < 3; ++change) {
+        launches = elsewhere = branches_used = 0;
+        CHECK(pond_batch_step(b, 2 * run) == POND_OK);
+        CHECK(launches == run * groups * (fused ? 1 : 2) && elsewhere == 0);
+        CHECK(branches_used == want_branches);
+        CHECK(fake::device == current && fake::captures == 0);
+        CHECK(pond_batch_remove(b, h[0].get()) == POND_OK && pond_batch_add(b, h[0].get()) == POND_OK);
+    }
+    for (int i = 0; i < groups; ++i) CHECK(h[i]->steps == 3 * 2 * run);
+    CHECK(pond_batch_destroy(b) == POND_OK);
+    CHECK(fake::streams == streams && fake::events == events);
+    fake::device = 0;
+}
+
+// the branches run on the batch's device, whichever is current; with fewer streams than asked for
+// there are fewer of them
+static void device()
+{
+    for (int current : {0, 1})
+        for (bool fused : {true, false}) {
+            step(1, fused, current, 1);
+            step(2, fused, current, 2);
+            step(6, fused, current, 3);
+        }
+}
+static void streams()
+{
+    for (int left : {2, 3}) { // the batch's own two, and none or one of the branches'
+        fake::streams_left = left;
+        step(4, true, 0, left - 1);
+    }
+}
+
+int main(int, char **argv)
+{
+    const std::string what = argv[1];
+    if (what == "device") device();
+    else if (what == "streams") streams();
+    else return 255;
+    return 0;
+}
