@@ -39,6 +39,7 @@ struct Group {
     int lanes;               // lanes per receiver
     int first, count;        // slot range in the descriptor arrays
     int st_tiles, fc_tiles;  // total tiles of the two step kernels
+    int branch = 0;          // of a long run
 };
 
 } // namespace
@@ -52,6 +53,7 @@ struct pond_batch {
     // built from the members on demand
     bool dirty = true;
     std::vector<Group> groups;
+    std::vector<int> by_size;            // groups, most tiles first
     std::vector<int> slot_of;            // member index -> slot
     std::vector<SlotDesc> desc_h;        // [2][slots]
     SlotDesc *desc_d = nullptr;
@@ -116,7 +118,7 @@ int rebuild(pond_batch *b)
         pond_handle *h = b->members[i];
         if (key(i) != gkey) {
             gkey = key(i);
-            b->groups.push_back(Group{h->lc.dim, h->lc.fp32, h->lc.stream_tile, h->lc.law, h->lc.lanes, s, 0, 0, 0});
+            b->groups.push_back(Group{h->lc.dim, h->lc.fp32, h->lc.stream_tile, h->lc.law, h->lc.lanes, s, 0, 0, 0, 0});
         }
         Group &g = b->groups.back();
         b->slot_of[i] = s;
@@ -130,6 +132,10 @@ int rebuild(pond_batch *b)
         g.st_tiles += h->st_tiles;
         g.fc_tiles += h->fc_tiles;
     }
+    b->by_size.resize(b->groups.size());
+    for (size_t g = 0; g < b->by_size.size(); ++g) b->by_size[g] = (int)g;
+    std::stable_sort(b->by_size.begin(), b->by_size.end(),
+                     [&](int x, int y) { return b->groups[x].st_tiles > b->groups[y].st_tiles; });
     if (M > 0 && hipMemcpy(b->desc_d, b->desc_h.data(), sizeof(SlotDesc) * R * M, hipMemcpyHostToDevice) != hipSuccess)
         return POND_E_DEVICE;
     b->phase = 0;
@@ -200,22 +206,20 @@ struct Branches {
 
 hipError_t enqueue_run(pond_batch *b, Branches &br, int steps, int arr)
 {
-    std::vector<const Group *> by_size;
-    for (const Group &g : b->groups) by_size.push_back(&g);
-    std::stable_sort(by_size.begin(), by_size.end(), [](auto *x, auto *y) { return x->st_tiles > y->st_tiles; });
-    std::vector<const Group *> of[kBranches];
+    // (nothing in an open capture allocates: an exception would leave it open)
     long long tiles[kBranches] = {0};
-    for (const Group *g : by_size) {
+    for (int g : b->by_size) {
         const int k = (int)(std::min_element(tiles, tiles + br.n) - tiles);
-        of[k].push_back(g);
-        tiles[k] += g->st_tiles;
+        b->groups[g].branch = k;
+        tiles[k] += b->groups[g].st_tiles;
     }
     hipError_t e = hipSuccess;
     for (int k = 1; k < br.n && e == hipSuccess; ++k) e = br.wait(br.st[k], br.st[0]);
     for (int k = 0; k < br.n; ++k)
         for (int s = 0; s < steps; ++s)
-            for (const Group *g : of[k])
-                if (e == hipSuccess) e = enqueue_group(b, *g, br.st[k], (arr + s) % b->states());
+            for (int g : b->by_size)
+                if (e == hipSuccess && b->groups[g].branch == k)
+                    e = enqueue_group(b, b->groups[g], br.st[k], (arr + s) % b->states());
     for (int k = 1; k < br.n; ++k) {
         const hipError_t ej = br.wait(br.st[0], br.st[k]); // (joined also after an error: the capture ends)
         if (e == hipSuccess) e = ej;

@@ -17,6 +17,17 @@ using namespace pond;
         }                                                      \
     } while (0)
 
+// memory for C++ objects that has run out while a capture is open
+static bool memory_short = false;
+void *operator new(size_t n)
+{
+    if (memory_short && fake::captures) throw std::bad_alloc();
+    if (void *p = std::malloc(n)) return p;
+    throw std::bad_alloc();
+}
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete(void *p, size_t) noexcept { std::free(p); }
+
 static int launches, elsewhere, branches_used;
 static hipStream_t seen[8];
 static hipError_t launched(const LaunchCtx &c)
@@ -97,11 +108,20 @@ static void streams()
     }
 }
 
+// a capture allocates nothing of its own: an exception there would leave the C entry with the
+// capture open
+static void memory()
+{
+    memory_short = true;
+    for (bool fused : {true, false}) step(6, fused, 0, 3);
+}
+
 int main(int, char **argv)
 {
     const std::string what = argv[1];
     if (what == "device") device();
     else if (what == "streams") streams();
+    else if (what == "memory") memory();
     else return 255;
     return 0;
 }

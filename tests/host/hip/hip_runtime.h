@@ -73,13 +73,14 @@ inline hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned)
     std::lock_guard<std::recursive_mutex> l(fake::lock);
     if (fake::streams_left-- <= 0) return hipErrorOutOfMemory;
     ++fake::streams;
-    return *s = new ihipStream_t{fake::device, nullptr}, hipSuccess;
+    *s = (hipStream_t)std::malloc(sizeof(ihipStream_t));
+    return **s = {fake::device, nullptr}, hipSuccess;
 }
 inline hipError_t hipStreamDestroy(hipStream_t s)
 {
     std::lock_guard<std::recursive_mutex> l(fake::lock);
     --fake::streams;
-    delete s;
+    std::free(s);
     return hipSuccess;
 }
 inline hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
@@ -88,13 +89,14 @@ inline hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned)
     std::lock_guard<std::recursive_mutex> l(fake::lock);
     if (fake::events_left-- <= 0) return hipErrorOutOfMemory;
     ++fake::events;
-    return *e = new ihipEvent_t{fake::device, nullptr}, hipSuccess;
+    *e = (hipEvent_t)std::malloc(sizeof(ihipEvent_t));
+    return **e = {fake::device, nullptr}, hipSuccess;
 }
 inline hipError_t hipEventDestroy(hipEvent_t e)
 {
     std::lock_guard<std::recursive_mutex> l(fake::lock);
     --fake::events;
-    delete e;
+    std::free(e);
     return hipSuccess;
 }
 inline hipError_t hipEventRecord(hipEvent_t e, hipStream_t s)
@@ -162,9 +164,9 @@ inline hipError_t hipStreamEndCapture(hipStream_t s, hipGraph_t *g)
 {
     --fake::captures;
     s->origin = nullptr;
-    return *g = new ihipGraph, hipSuccess;
+    return *g = (ihipGraph *)std::malloc(1), hipSuccess;
 }
-inline hipError_t hipGraphDestroy(hipGraph_t g) { return delete g, hipSuccess; }
-inline hipError_t hipGraphInstantiate(hipGraphExec_t *x, hipGraph_t, void *, char *, size_t) { return *x = new ihipGraph, hipSuccess; }
-inline hipError_t hipGraphExecDestroy(hipGraphExec_t x) { return delete x, hipSuccess; }
+inline hipError_t hipGraphDestroy(hipGraph_t g) { return std::free(g), hipSuccess; }
+inline hipError_t hipGraphInstantiate(hipGraphExec_t *x, hipGraph_t, void *, char *, size_t) { return *x = (ihipGraph *)std::malloc(1), hipSuccess; }
+inline hipError_t hipGraphExecDestroy(hipGraphExec_t x) { return std::free(x), hipSuccess; }
 inline hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) { return hipSuccess; }
