@@ -19,10 +19,11 @@ FLOPs of the streaming kernel (the dominant one), per receiver, for the moment-f
 reconstruction.  The last pass: every set (f, g) has NF moment fields; each field is
 interpolated at the departure points of all Q directions with separable cubic weights
 (x: 3 departure abscissae x 5 window rows x 4 taps; y: Q directions x 4 taps) and
-contracted into the Q populations (one multiply and one FMA each).  The passes before it
-need only the sums rho, J and 2 rho E of the populations, whose weights fold over the
-directions of each axis: 45 FMA in x and 4 in the other axes per row of 15 window values
-of f and g, and 75 FMA per axis to fold.  A FMA counts as two flops.  The weights,
+contracted into the Q populations (one multiply and one FMA each).  In two and three
+dimensions the passes before it need only the sums rho, J and 2 rho E of the populations,
+whose weights fold over the directions of each axis: 45 FMA in x and 4 in the other axes
+per row of 15 window values of f and g, and 75 FMA per axis to fold.  One dimension forms
+the populations in every pass.  A FMA counts as two flops.  The weights,
 Lagrange coefficients, moments and EoS of a pass, the donor moments of the tile and the
 output moments are added as fixed terms.
 """
@@ -97,8 +98,7 @@ def collide_flops_per_node(dim: int) -> int:
 
 
 def stream_flops_per_node(dim: int, n_pass: int) -> int:
-    rows = 15 ** (dim - 1)                              # window rows of the moments: (3 x 5) per further axis
-    sums = 2 * rows * (45 + (4 if dim > 1 else 0)) + 2 * 75 * dim
+    sums = 2 * 15 ** (dim - 1) * 49 + 2 * 75 * dim       # 15 = 3 x 5 window rows per axis beyond x
     if dim == 3:
         # per z-window plane and z power: the D2Q9 x-y contraction of 9 fields (972 FMA
         # with the zero taps) and 27 FMA of the z contraction; 5 planes x 3 powers per set
@@ -117,4 +117,5 @@ def stream_flops_per_node(dim: int, n_pass: int) -> int:
         fixed_pass = 3 * 16 + 20 + 18 + 20
         donor = 60
         out = 60
+        sums = fields * per_field
     return fields * per_field + (n_pass - 1) * sums + n_pass * fixed_pass + donor + out
