@@ -201,6 +201,8 @@ hipError_t launch_step_double_windows(const LaunchCtx &c, const SlotDesc *slots,
 hipError_t launch_collide_check(const LaunchCtx &c, const SlotDesc *slots, int nslots, int tiles);
 // equation-of-state variant of a configuration's step kernels
 inline int step_law(int dieterici, int isothermal) { return isothermal ? kIsothermal : dieterici ? kDieterici : kLean; }
+// tile shapes that have a kernel with one lane a receiver
+constexpr bool one_lane_shape(int tx, int ty) { return tx * ty == 256 && ty >= 8; }
 // lanes per receiver for a lattice of `tiles` tiles of the current shape: a choice of the
 // lattice alone, so that it runs the same kernel by itself and in a batch
 int step_lanes(const LaunchCtx &c, int tiles);

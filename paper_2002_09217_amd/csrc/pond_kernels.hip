@@ -261,8 +261,11 @@ static hipError_t launch_stream_t(const LaunchCtx &c, const SlotDesc *slots, int
 template <typename PopT, typename LdsT, int TX, int TY>
 static hipError_t launch_stream_l(const LaunchCtx &c, const SlotDesc *slots, int nslots, int tiles)
 {
-    if constexpr (TX * TY == 256 && TY >= 8) // the shapes of step_lanes
+    if constexpr (one_lane_shape(TX, TY)) {
         if (c.lanes == 1) return launch_stream_t<2, 1, PopT, LdsT, TX, TY>(c, slots, nslots, tiles);
+    } else if (c.lanes == 1) {
+        return hipErrorInvalidValue;
+    }
     return launch_stream_t<2, 2, PopT, LdsT, TX, TY>(c, slots, nslots, tiles);
 }
 
@@ -704,7 +707,6 @@ hipError_t launch_collide_check(const LaunchCtx &c, const SlotDesc *slots, int n
 // overlap on a CU: 2048^2 878 us against 1224 (FP64, 16 x 16), 702 against 1103 (FP32).
 // Tiles of fewer receivers would leave workgroups of two waves (16 x 8: 1072 us), and two 64 x
 // 4 tiles do not fit a CU's LDS in FP64.
-static bool one_lane_shape(int tx, int ty) { return tx * ty == 256 && ty >= 8; }
 int step_lanes(const LaunchCtx &c, int tiles)
 {
     int tx, ty;

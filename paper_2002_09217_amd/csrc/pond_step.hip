@@ -368,8 +368,11 @@ static hipError_t launch_step_t(const LaunchCtx &c, const SlotDesc *slots, int n
 template <bool MIXED, typename LdsT, int TX, int TY>
 static hipError_t launch_step_l(const LaunchCtx &c, const SlotDesc *slots, int nslots, int tiles)
 {
-    if constexpr (TX * TY == 256 && TY >= 8) // the shapes of step_lanes
+    if constexpr (one_lane_shape(TX, TY)) {
         if (c.lanes == 1) return launch_step_t<2, 1, MIXED, LdsT, TX, TY>(c, slots, nslots, tiles);
+    } else if (c.lanes == 1) {
+        return hipErrorInvalidValue;
+    }
     return launch_step_t<2, 2, MIXED, LdsT, TX, TY>(c, slots, nslots, tiles);
 }
 
