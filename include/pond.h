@@ -215,8 +215,9 @@ int pond_footprint(const pond_config *cfg, unsigned long long *bytes);
 
 /* ---------------------------------------------------------------------------
  * Batches: many independent lattices advanced together.  Every step of a batch is
- * one launch of each step kernel per group of members that share dim, precision and
- * streaming tile shape, over the tiles of all of them; each member keeps its own
+ * one launch of each step kernel per group of members that share dim, precision,
+ * streaming tile shape, equation-of-state variant and lanes per receiver, over the
+ * tiles of all of them; each member keeps its own
  * device state, parameters, error flags and step counter, so its results are
  * bitwise those of pond_step on the same handle alone.  The main-text time step of
  * each lattice is unchanged (eqs. 1-22); batching is scheduling only.

@@ -3,9 +3,9 @@
 // error flags and step counter, and each step kernel reads a member's descriptor
 // exactly as it does for a lattice stepped alone, so results are bitwise identical.
 //
-// Members that share (dim, precision, tile shape, equation-of-state variant) form a
-// group; a batch step is one launch of each step kernel per group over the
-// concatenated tiles of its members.  The members of a batch share the form of the step (fused, or two
+// Members that share (dim, precision, tile shape, equation-of-state variant, lanes per
+// receiver) form a group; a batch step is one launch of each step kernel per group over
+// the concatenated tiles of its members.  The members of a batch share the form of the step (fused, or two
 // kernels), which fixes the number of state buffers or ring slots R (3 or 2) they cycle
 // through.  R descriptor arrays per batch: array a holds, for every member, the
 // descriptor reading the state a steps after the one current when the arrays were built;

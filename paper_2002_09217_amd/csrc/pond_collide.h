@@ -99,9 +99,10 @@ __device__ __forceinline__ void korteweg_force(const double *Kxx, const double *
 
 // Thermodynamic state of a node from its streamed density, gauge velocity, g sum
 // (2 rho E) and force: u-hat = u + F dt/(2 rho), e = E - |u-hat|^2/2, T and p from the
-// EoS, h = e + p/rho, the heat-flux potential (visc = mu/p).  Writes the fields of an LDS thermodynamic region (field stride `stride`) at index li; returns the
-// admissibility bits.  LAW = kLean: the van der Waals fluid with its energy equation only
-// (the lean variant of the streaming kernels).
+// EoS, h = e + p/rho, the heat-flux potential (visc = mu/p).  Writes the fields of an LDS
+// thermodynamic region (field stride `stride`) at index li; returns the admissibility bits.
+// LAW = kLean: the van der Waals fluid with its energy equation only (the lean variant of the
+// streaming kernels).
 template <int DIM, int LAW = kAnyLaw, typename PT>
 __device__ __forceinline__ int thermo_state(const PT &P, double rho, double ux, double uy, double G0, double Fx,
                                             double Fy, double visc, double *th, int stride, int li)

@@ -47,7 +47,8 @@ constexpr bool kDeviationStore = sizeof(PopT) == 4;
 // isothermal runs of any law (kIsothermal) and for the Dieterici fluid with its energy
 // (kDieterici), so that the first two carry none of the third's code: its temperature is an
 // out-of-line Newton iteration, around which a kernel spills what it holds.  The others
-// (collision, check, read-back) take any law (kAnyLaw).
+// (k_force_collide, which is the second kernel of the two-kernel step and the check and
+// read-back of the fused one, and the D3Q27 closure) take any law (kAnyLaw).
 // ---------------------------------------------------------------------------
 enum { kEosVdw = 0, kEosDieterici = 1, kEosWell = 2 };
 template <int LAW = kAnyLaw, typename PT>

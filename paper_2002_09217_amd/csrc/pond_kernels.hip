@@ -702,11 +702,17 @@ hipError_t launch_collide_check(const LaunchCtx &c, const SlotDesc *slots, int n
 }
 
 // Two lanes a receiver fill a CU with one 512-lane workgroup, which is as much as there is up
-// to one tile per CU: 256^2 FP64 18.7 us against 20.2 with one lane.  Beyond that one lane
-// leaves the receiver's weights to be computed once and two or three 256-lane workgroups to
-// overlap on a CU: 2048^2 878 us against 1224 (FP64, 16 x 16), 702 against 1103 (FP32).
-// Tiles of fewer receivers would leave workgroups of two waves (16 x 8: 1072 us), and two 64 x
-// 4 tiles do not fit a CU's LDS in FP64.
+// to one tile per CU: 256^2 (256 tiles of 16 x 16) FP64 19.9 us against 21.1 with one lane, FP32
+// 17.9 against 20.6.  Beyond that one lane leaves the receiver's weights to be computed once
+// and two or three 256-lane workgroups to overlap on a CU.  One against two lanes, fused
+// step in 16 x 16 tiles, FP64 / FP32 in us: 272^2 (289 tiles) 28.8 / 25.9 against 36.4 / 30.4;
+// 384^2 43.0 / 34.6 against 54.3 / 45.2; 512^2 58.4 / 48.1 against 74.9 / 62.9; 1024^2 217 /
+// 156 against 310 / 218; 2048^2 858 / 654 against 1192 / 921, and against the best shape of
+// two, 16 x 8, 1108 / 872.  Streaming alone, other sizes between, one and three passes and 32 x
+// 8 tiles show the same; just above 256 tiles the tuner's best of two lanes is level
+// (256 x 264: 29.7 / 24.1 in 16 x 8 tiles, 28.6 / 24.3 with one).
+// Tiles of fewer receivers would leave workgroups of two waves, and two 64 x 4 tiles do not fit
+// a CU's LDS in FP64.
 int step_lanes(const LaunchCtx &c, int tiles)
 {
     int tx, ty;

@@ -238,7 +238,8 @@ __device__ __forceinline__ void store_donor_moments(const SlotDesc &S, size_t N,
 constexpr int kColumnsAhead = 3;
 
 // weight of window column j (0..4) in the cubic stencil of departure velocity v: the
-// column weights of window_weights, one at a time (its halo check is not repeated)
+// column weights of window_weights to round-off (which forms them all from common factors),
+// one at a time and without its halo check
 __device__ __forceinline__ double window_tap(double v, double dt, int j)
 {
     const double d = -v * dt;
@@ -346,11 +347,12 @@ __device__ __forceinline__ double pair_sum(double v)
 // over the moments and the 5 x 5 x 5 window: 49 FMA per row of fifteen values of f and
 // of g, against 2 x 57 for the populations.  With two passes this took k3_stream from
 // 53.6 to 43.7 ms (FP64) and from 32.1 to 26.1 ms (FP32) at 256^3: fewer FMA, half the LDS
-// reads a pass (the pairs are read 16 bytes a lane, at twice the rate of 8), and the last
-// pass, now outside the pass loop, spills 68 bytes a lane instead of 272 (FP64 184, 396).
+// reads a pass (the pairs are read 16 bytes a lane, at twice the rate of 8).  The last pass,
+// now outside the pass loop, needed 68 bytes of scratch a lane instead of 272 (FP64 184, 396);
+// the columns and rounds read ahead since, which pay for it, take 144 (FP64 432).
 //
-// Each lane of a receiver takes half the rows (y index n, window row r) of both sets, so a window value pair (f, g) is one wide
-// LDS read and the lanes share the work evenly.
+// Each lane of a receiver takes half the rows (y index n, window row r) of both sets, so a
+// window value pair (f, g) is one wide LDS read and the lanes share the work evenly.
 // ---------------------------------------------------------------------------
 template <typename LdsT, int LN> struct SumRow; // staged layout of the sums passes
 template <int LN> struct SumRow<double, LN> {
@@ -454,9 +456,10 @@ __global__ void __launch_bounds__(2 * TX *TY, sizeof(LdsT) == 4 ? 3 : 2) k3_stre
     __shared__ LdsT ref[kDev ? 54 : 1];
     // z coefficients of the pass, per receiver: the FP32 window keeps the 45 products
     // C_mo wz_m[sz] of its rounds, the FP64 window the nine C_mo and fifteen wz_m[sz] whose
-    // product each round forms (23 and 25 KB of LDS)
+    // product each round forms
     constexpr int NR = TX * TY;
-    // (a sums pass keeps the fifteen g0 and fifteen g1 instead)
+    // (a sums pass keeps the fifteen g0 and fifteen g1 instead; 23 KB of LDS in FP32, 31 in
+    // FP64, whose workgroup so takes 66 of the 160 KB that two share)
     constexpr int kCz = kDev ? 45 : 30;
     __shared__ AccT s_cz[kCz * NR];
     __shared__ int s_wfast[NT / 64]; // per wave: its lanes allow the zero-tap-free window
