@@ -30,16 +30,12 @@ namespace {
 // largest tile count of one launch: keeps blocks x threads per block below 2^31
 constexpr long long kMaxLaunchTiles = 1LL << 21;
 
-// most branches of a captured run: the process has four hardware queues
-constexpr int kBranches = 3;
-
 struct Group {
     int dim, fp32, tile;
     int law;                 // equation-of-state variant of the step kernels
     int lanes;               // lanes per receiver
     int first, count;        // slot range in the descriptor arrays
     int st_tiles, fc_tiles;  // total tiles of the two step kernels
-    int branch = 0;          // of a long run
 };
 
 } // namespace
@@ -48,12 +44,10 @@ struct pond_batch {
     hipStream_t stream = nullptr;
     bool own_stream = false;
     hipStream_t capture_stream = nullptr;
-    hipStream_t branch[kBranches - 1] = {}; // streams beside it in long runs, made when first needed
     std::vector<pond_handle *> members;  // order of addition
     // built from the members on demand
     bool dirty = true;
     std::vector<Group> groups;
-    std::vector<int> by_size;            // groups, most tiles first
     std::vector<int> slot_of;            // member index -> slot
     std::vector<SlotDesc> desc_h;        // [2][slots]
     SlotDesc *desc_d = nullptr;
@@ -118,7 +112,7 @@ int rebuild(pond_batch *b)
         pond_handle *h = b->members[i];
         if (key(i) != gkey) {
             gkey = key(i);
-            b->groups.push_back(Group{h->lc.dim, h->lc.fp32, h->lc.stream_tile, h->lc.law, h->lc.lanes, s, 0, 0, 0, 0});
+            b->groups.push_back(Group{h->lc.dim, h->lc.fp32, h->lc.stream_tile, h->lc.law, h->lc.lanes, s, 0, 0, 0});
         }
         Group &g = b->groups.back();
         b->slot_of[i] = s;
@@ -132,10 +126,6 @@ int rebuild(pond_batch *b)
         g.st_tiles += h->st_tiles;
         g.fc_tiles += h->fc_tiles;
     }
-    b->by_size.resize(b->groups.size());
-    for (size_t g = 0; g < b->by_size.size(); ++g) b->by_size[g] = (int)g;
-    std::stable_sort(b->by_size.begin(), b->by_size.end(),
-                     [&](int x, int y) { return b->groups[x].st_tiles > b->groups[y].st_tiles; });
     if (M > 0 && hipMemcpy(b->desc_d, b->desc_h.data(), sizeof(SlotDesc) * R * M, hipMemcpyHostToDevice) != hipSuccess)
         return POND_E_DEVICE;
     b->phase = 0;
@@ -143,88 +133,25 @@ int rebuild(pond_batch *b)
     return POND_OK;
 }
 
-hipError_t enqueue_group(pond_batch *b, const Group &g, hipStream_t st, int arr)
-{
-    LaunchCtx c{g.dim, 0, 0, 0, g.fp32, st, g.tile};
-    c.law = g.law;
-    c.lanes = g.lanes;
-    c.fused = b->fused;
-    const SlotDesc *d = b->desc_d + (size_t)arr * b->members.size() + g.first;
-    if (b->fused) return launch_step_fused(c, d, g.count, g.st_tiles);
-    const hipError_t e = launch_stream(c, d, g.count, g.st_tiles);
-    return e == hipSuccess ? launch_force_collide(c, d, g.count, g.fc_tiles) : e;
-}
-
 hipError_t enqueue_step(pond_batch *b, hipStream_t st, int arr)
 {
+    const int M = (int)b->members.size();
     for (const Group &g : b->groups) {
-        const hipError_t e = enqueue_group(b, g, st, arr);
+        LaunchCtx c{g.dim, 0, 0, 0, g.fp32, st, g.tile};
+        c.law = g.law;
+        c.lanes = g.lanes;
+        c.fused = b->fused;
+        const SlotDesc *d = b->desc_d + (size_t)arr * M + g.first;
+        hipError_t e;
+        if (b->fused) {
+            e = launch_step_fused(c, d, g.count, g.st_tiles);
+        } else {
+            e = launch_stream(c, d, g.count, g.st_tiles);
+            if (e == hipSuccess) e = launch_force_collide(c, d, g.count, g.fc_tiles);
+        }
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
-}
-
-// A long run in branches: no group reads what another writes, so each branch takes some of the
-// groups through all steps of the run, and the launches of a group that leaves the chip idle
-// run beside another's (one after another, the last blocks of each launch drain first).
-// Two jobs each of 64^2, 128^2, 256^2 and 512^2 (three groups), FP32: 135.6 -> 120.5 us a step.
-// A short run stays in one branch: a fork and a join cost about what its three steps gain.
-// At most kBranches of them, the groups spread by their tiles.
-struct Branches {
-    int n = 1;
-    hipStream_t st[kBranches];
-    int events = 0;
-    hipEvent_t ev[2 * kBranches]; // (live until the capture has ended)
-    // at most `most` of them, fewer where a stream cannot be had; the streams stay with the batch
-    Branches(pond_batch *b, int most)
-    {
-        st[0] = b->capture_stream;
-        for (; n < most; ++n) {
-            hipStream_t &s = b->branch[n - 1];
-            if (!s && hipStreamCreateWithFlags(&s, hipStreamNonBlocking) != hipSuccess) {
-                s = nullptr;
-                (void)hipGetLastError();
-                break;
-            }
-            st[n] = s;
-        }
-    }
-    Branches(const Branches &) = delete;
-    ~Branches()
-    {
-        for (int k = 0; k < events; ++k) (void)hipEventDestroy(ev[k]);
-    }
-    hipError_t wait(hipStream_t waits, hipStream_t on)
-    {
-        hipError_t e = hipEventCreateWithFlags(&ev[events], hipEventDisableTiming);
-        if (e != hipSuccess) return e;
-        ++events;
-        e = hipEventRecord(ev[events - 1], on);
-        return e == hipSuccess ? hipStreamWaitEvent(waits, ev[events - 1], 0) : e;
-    }
-};
-
-hipError_t enqueue_run(pond_batch *b, Branches &br, int steps, int arr)
-{
-    // (nothing in an open capture allocates: an exception would leave it open)
-    long long tiles[kBranches] = {0};
-    for (int g : b->by_size) {
-        const int k = (int)(std::min_element(tiles, tiles + br.n) - tiles);
-        b->groups[g].branch = k;
-        tiles[k] += b->groups[g].st_tiles;
-    }
-    hipError_t e = hipSuccess;
-    for (int k = 1; k < br.n && e == hipSuccess; ++k) e = br.wait(br.st[k], br.st[0]);
-    for (int k = 0; k < br.n; ++k)
-        for (int s = 0; s < steps; ++s)
-            for (int g : b->by_size)
-                if (e == hipSuccess && b->groups[g].branch == k)
-                    e = enqueue_group(b, b->groups[g], br.st[k], (arr + s) % b->states());
-    for (int k = 1; k < br.n; ++k) {
-        const hipError_t ej = br.wait(br.st[0], br.st[k]); // (joined also after an error: the capture ends)
-        if (e == hipSuccess) e = ej;
-    }
-    return e;
 }
 
 // fused steps: the closure check of every member's state read by descriptor array `arr`
@@ -246,17 +173,15 @@ bool build_step_graph(pond_batch *b, int kind, int arr)
     hipGraphExec_t &exec = b->step_exec[kind][arr];
     if (exec) return true;
     hipGraph_t g = nullptr;
-    // the branches' streams and events are the batch's device's, whichever is current now
-    const StreamDevice on(b->capture_stream);
-    Branches br(b, kind == 1 && on.status == hipSuccess ? std::min(kBranches, (int)b->groups.size()) : 1);
     if (hipStreamBeginCapture(b->capture_stream, hipStreamCaptureModeThreadLocal) != hipSuccess) return false;
-    const hipError_t er = enqueue_run(b, br, b->run(kind), arr);
+    hipError_t e = hipSuccess;
+    for (int k = 0; k < b->run(kind) && e == hipSuccess; ++k) e = enqueue_step(b, b->capture_stream, (arr + k) % b->states());
     const hipError_t ec = hipStreamEndCapture(b->capture_stream, &g);
-    if (er != hipSuccess || ec != hipSuccess || !g) {
+    if (e != hipSuccess || ec != hipSuccess || !g) {
         if (g) (void)hipGraphDestroy(g);
         return false;
     }
-    const hipError_t e = hipGraphInstantiate(&exec, g, nullptr, nullptr, 0);
+    e = hipGraphInstantiate(&exec, g, nullptr, nullptr, 0);
     (void)hipGraphDestroy(g);
     if (e != hipSuccess) {
         exec = nullptr;
@@ -415,8 +340,6 @@ int pond_batch_destroy(pond_batch *b)
     if (b->desc_d) (void)hipFree(b->desc_d);
     if (b->flags_d) (void)hipFree(b->flags_d);
     if (b->capture_stream) (void)hipStreamDestroy(b->capture_stream);
-    for (hipStream_t s : b->branch)
-        if (s) (void)hipStreamDestroy(s);
     if (b->own_stream && b->stream) (void)hipStreamDestroy(b->stream);
     delete b;
     return POND_OK;

@@ -28,15 +28,11 @@ void *operator new(size_t n)
 void operator delete(void *p) noexcept { std::free(p); }
 void operator delete(void *p, size_t) noexcept { std::free(p); }
 
-static int launches, elsewhere, branches_used;
-static hipStream_t seen[8];
+static int launches, elsewhere;
 static hipError_t launched(const LaunchCtx &c)
 {
     ++launches;
     if (fake::device_of(c.st) != 0) ++elsewhere; // the members' memory is on device 0
-    int k = 0;
-    while (k < branches_used && seen[k] != c.st) ++k;
-    if (k == branches_used && k < 8) seen[branches_used++] = c.st;
     return hipSuccess;
 }
 namespace pond {
@@ -62,7 +58,7 @@ static std::unique_ptr<pond_handle> member(int tile, bool fused)
 }
 
 // a batch on device 0 of `groups` groups, stepped while `current` is the current device
-static void step(int groups, bool fused, int current, int want_branches)
+static void step(int groups, bool fused, int current)
 {
     const int streams = fake::streams, events = fake::events;
     pond_batch *b = nullptr;
@@ -76,10 +72,9 @@ static void step(int groups, bool fused, int current, int want_branches)
     fake::device = current;
     const int run = fused ? kFusedRun : 2 * kRunPairs;
     for (int change = 0; change < 3; ++change) {
-        launches = elsewhere = branches_used = 0;
+        launches = elsewhere = 0;
         CHECK(pond_batch_step(b, 2 * run) == POND_OK);
         CHECK(launches == run * groups * (fused ? 1 : 2) && elsewhere == 0);
-        CHECK(branches_used == want_branches);
         CHECK(fake::device == current && fake::captures == 0);
         CHECK(pond_batch_remove(b, h[0].get()) == POND_OK && pond_batch_add(b, h[0].get()) == POND_OK);
     }
@@ -89,23 +84,12 @@ static void step(int groups, bool fused, int current, int want_branches)
     fake::device = 0;
 }
 
-// the branches run on the batch's device, whichever is current; with fewer streams than asked for
-// there are fewer of them
+// a batch's runs are captured for its own device, whichever is current
 static void device()
 {
     for (int current : {0, 1})
-        for (bool fused : {true, false}) {
-            step(1, fused, current, 1);
-            step(2, fused, current, 2);
-            step(6, fused, current, 3);
-        }
-}
-static void streams()
-{
-    for (int left : {2, 3}) { // the batch's own two, and none or one of the branches'
-        fake::streams_left = left;
-        step(4, true, 0, left - 1);
-    }
+        for (bool fused : {true, false})
+            for (int groups : {1, 2, 6}) step(groups, fused, current);
 }
 
 // a capture allocates nothing of its own: an exception there would leave the C entry with the
@@ -113,14 +97,13 @@ static void streams()
 static void memory()
 {
     memory_short = true;
-    for (bool fused : {true, false}) step(6, fused, 0, 3);
+    for (bool fused : {true, false}) step(6, fused, 0);
 }
 
 int main(int, char **argv)
 {
     const std::string what = argv[1];
     if (what == "device") device();
-    else if (what == "streams") streams();
     else if (what == "memory") memory();
     else return 255;
     return 0;
