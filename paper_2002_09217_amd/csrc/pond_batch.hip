@@ -10,7 +10,7 @@
 // through.  R descriptor arrays per batch: array a holds, for every member, the
 // descriptor reading the state a steps after the one current when the arrays were built;
 // steps cycle through them, so runs of a multiple of R steps replay one captured HIP
-// graph.  A run of fused steps ends with the closure check of every member's last state.
+// graph (long runs: one for each stream that takes some of the groups).  A run of fused steps ends with the closure check of every member's last state.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -30,12 +30,16 @@ namespace {
 // largest tile count of one launch: keeps blocks x threads per block below 2^31
 constexpr long long kMaxLaunchTiles = 1LL << 21;
 
+// streams that long runs use at most: the process has four hardware queues
+constexpr int kStreams = 3;
+
 struct Group {
     int dim, fp32, tile;
     int law;                 // equation-of-state variant of the step kernels
     int lanes;               // lanes per receiver
     int first, count;        // slot range in the descriptor arrays
     int st_tiles, fc_tiles;  // total tiles of the two step kernels
+    int stream;              // of its long runs (0: the batch's own)
 };
 
 } // namespace
@@ -44,6 +48,11 @@ struct pond_batch {
     hipStream_t stream = nullptr;
     bool own_stream = false;
     hipStream_t capture_stream = nullptr;
+    // streams beside `stream` for long runs, of its device, made when first needed, and the events
+    // that fork them from it and join them again
+    hipStream_t beside[kStreams - 1] = {};
+    hipEvent_t fork = nullptr, join[kStreams - 1] = {};
+    int streams = 1;                     // that the long runs of the present groups use
     std::vector<pond_handle *> members;  // order of addition
     // built from the members on demand
     bool dirty = true;
@@ -57,8 +66,8 @@ struct pond_batch {
     int phase = 0;                       // descriptor array reading the current states
     bool fused = false;                  // form of the step of every member
     // [0]: the short run, [1]: the long run of steps (run_length); each starting from
-    // descriptor array a
-    hipGraphExec_t step_exec[2][kFusedRing] = {};
+    // descriptor array a; a long run as one graph for each stream
+    hipGraphExec_t step_exec[2][kFusedRing][kStreams] = {};
     bool graphs_ok = true;
     int states() const { return fused ? kFusedRing : 2; }
     int run(int kind) const { return fused ? (kind ? kFusedRun : kFusedRing) : (kind ? 2 * kRunPairs : 2); }
@@ -69,11 +78,48 @@ namespace {
 void drop_graphs(pond_batch *b)
 {
     for (auto &kind : b->step_exec)
-        for (auto &g : kind)
-            if (g) {
-                (void)hipGraphExecDestroy(g);
-                g = nullptr;
+        for (auto &from : kind)
+            for (auto &g : from)
+                if (g) {
+                    (void)hipGraphExecDestroy(g);
+                    g = nullptr;
+                }
+}
+
+// Long runs take the groups side by side: no group reads what another writes, so each stream
+// takes some of them through all steps, and the launches of a group that leaves the chip idle
+// run beside another's (one after another, the last blocks of each launch drain first).
+// Short runs and single steps stay on the batch's stream.
+//
+// Spreads the groups by their tiles, the largest first, over the batch's stream and those beside
+// it, of which it makes what is missing (fewer where one cannot be had).
+void spread_groups(pond_batch *b)
+{
+    const int want = std::min(kStreams, (int)b->groups.size());
+    b->streams = 1;
+    if (want > 1) {
+        const StreamDevice on(b->stream);
+        auto event = [](hipEvent_t &e) {
+            if (!e && hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) e = nullptr;
+            return e != nullptr;
+        };
+        if (on.status == hipSuccess && event(b->fork))
+            for (; b->streams < want; ++b->streams) {
+                hipStream_t &st = b->beside[b->streams - 1];
+                if (!st && hipStreamCreateWithFlags(&st, hipStreamNonBlocking) != hipSuccess) st = nullptr;
+                if (!st || !event(b->join[b->streams - 1])) break;
             }
+        if (b->streams < want) (void)hipGetLastError();
+    }
+    long long tiles[kStreams] = {0};
+    for (Group &g : b->groups) g.stream = -1;
+    for (size_t k = 0; k < b->groups.size(); ++k) {
+        Group *most = nullptr;
+        for (Group &g : b->groups)
+            if (g.stream < 0 && (!most || g.st_tiles > most->st_tiles)) most = &g;
+        most->stream = (int)(std::min_element(tiles, tiles + b->streams) - tiles);
+        tiles[most->stream] += most->st_tiles;
+    }
 }
 
 // regroup the members and upload the descriptor arrays
@@ -112,7 +158,7 @@ int rebuild(pond_batch *b)
         pond_handle *h = b->members[i];
         if (key(i) != gkey) {
             gkey = key(i);
-            b->groups.push_back(Group{h->lc.dim, h->lc.fp32, h->lc.stream_tile, h->lc.law, h->lc.lanes, s, 0, 0, 0});
+            b->groups.push_back(Group{h->lc.dim, h->lc.fp32, h->lc.stream_tile, h->lc.law, h->lc.lanes, s, 0, 0, 0, 0});
         }
         Group &g = b->groups.back();
         b->slot_of[i] = s;
@@ -126,6 +172,7 @@ int rebuild(pond_batch *b)
         g.st_tiles += h->st_tiles;
         g.fc_tiles += h->fc_tiles;
     }
+    spread_groups(b);
     if (M > 0 && hipMemcpy(b->desc_d, b->desc_h.data(), sizeof(SlotDesc) * R * M, hipMemcpyHostToDevice) != hipSuccess)
         return POND_E_DEVICE;
     b->phase = 0;
@@ -133,10 +180,12 @@ int rebuild(pond_batch *b)
     return POND_OK;
 }
 
-hipError_t enqueue_step(pond_batch *b, hipStream_t st, int arr)
+// a step of the groups of one stream (-1: of all)
+hipError_t enqueue_step(pond_batch *b, hipStream_t st, int arr, int of = -1)
 {
     const int M = (int)b->members.size();
     for (const Group &g : b->groups) {
+        if (of >= 0 && g.stream != of) continue;
         LaunchCtx c{g.dim, 0, 0, 0, g.fp32, st, g.tile};
         c.law = g.law;
         c.lanes = g.lanes;
@@ -167,15 +216,14 @@ hipError_t enqueue_check(pond_batch *b, hipStream_t st, int arr)
     return hipSuccess;
 }
 
-// record a run of b->run(kind) steps from descriptor array `arr`
-bool build_step_graph(pond_batch *b, int kind, int arr)
+// record a run of b->run(kind) steps from descriptor array `arr`: of all groups, or of those of
+// one stream
+bool record_run(pond_batch *b, int kind, int arr, int of, hipGraphExec_t &exec)
 {
-    hipGraphExec_t &exec = b->step_exec[kind][arr];
-    if (exec) return true;
     hipGraph_t g = nullptr;
     if (hipStreamBeginCapture(b->capture_stream, hipStreamCaptureModeThreadLocal) != hipSuccess) return false;
     hipError_t e = hipSuccess;
-    for (int k = 0; k < b->run(kind) && e == hipSuccess; ++k) e = enqueue_step(b, b->capture_stream, (arr + k) % b->states());
+    for (int k = 0; k < b->run(kind) && e == hipSuccess; ++k) e = enqueue_step(b, b->capture_stream, (arr + k) % b->states(), of);
     const hipError_t ec = hipStreamEndCapture(b->capture_stream, &g);
     if (e != hipSuccess || ec != hipSuccess || !g) {
         if (g) (void)hipGraphDestroy(g);
@@ -188,6 +236,43 @@ bool build_step_graph(pond_batch *b, int kind, int arr)
         return false;
     }
     return true;
+}
+
+bool build_step_graph(pond_batch *b, int kind, int arr)
+{
+    const int n = kind ? b->streams : 1;
+    for (int k = 0; k < n; ++k) {
+        hipGraphExec_t &exec = b->step_exec[kind][arr][k];
+        if (!exec && !record_run(b, kind, arr, n > 1 ? k : -1, exec)) return false;
+    }
+    return true;
+}
+
+// `runs` recorded runs; the batch's stream goes on when those beside it have ended
+hipError_t launch_runs(pond_batch *b, int kind, int arr, int runs)
+{
+    const int n = kind ? b->streams : 1;
+    hipError_t e = n > 1 ? hipEventRecord(b->fork, b->stream) : hipSuccess;
+    for (int k = 1; k < n && e == hipSuccess; ++k) e = hipStreamWaitEvent(b->beside[k - 1], b->fork, 0);
+    for (int r = 0; r < runs; ++r)
+        for (int k = 0; k < n && e == hipSuccess; ++k)
+            e = hipGraphLaunch(b->step_exec[kind][arr][k], k ? b->beside[k - 1] : b->stream);
+    for (int k = 1; k < n && e == hipSuccess; ++k) {
+        e = hipEventRecord(b->join[k - 1], b->beside[k - 1]);
+        if (e == hipSuccess) e = hipStreamWaitEvent(b->stream, b->join[k - 1], 0);
+    }
+    return e;
+}
+
+// waits for the batch's stream, and for those beside it, which then hold no command of a graph
+hipError_t finish(pond_batch *b)
+{
+    hipError_t e = hipStreamSynchronize(b->stream);
+    for (hipStream_t st : b->beside) {
+        const hipError_t es = st ? hipStreamSynchronize(st) : hipSuccess;
+        if (e == hipSuccess) e = es;
+    }
+    return e;
 }
 
 int find_member(const pond_batch *b, const pond_handle *h)
@@ -289,8 +374,11 @@ int pond_batch_step(pond_batch *b, int nsteps)
             b->graphs_ok = false;
             break;
         }
-        for (; left >= len; left -= len)
-            if (hipGraphLaunch(b->step_exec[kind][arr], b->stream) != hipSuccess) return POND_E_DEVICE;
+        if (launch_runs(b, kind, arr, left / len) != hipSuccess) {
+            (void)finish(b);
+            return POND_E_DEVICE;
+        }
+        left %= len;
     }
     for (; left > 0; --left) {
         if (enqueue_step(b, b->stream, arr) != hipSuccess) return POND_E_DEVICE;
@@ -300,7 +388,7 @@ int pond_batch_step(pond_batch *b, int nsteps)
     if (launch_gather_slot_flags(b->stream, b->desc_d, M, b->flags_d) != hipSuccess) return POND_E_DEVICE;
     if (hipMemcpyAsync(b->flags_h.data(), b->flags_d, sizeof(int) * kFlagWords * M, hipMemcpyDeviceToHost,
                        b->stream) != hipSuccess ||
-        hipStreamSynchronize(b->stream) != hipSuccess)
+        finish(b) != hipSuccess)
         return POND_E_DEVICE;
     b->phase = arr;
     // every member moves on by its own count of completed steps; failed ones leave
@@ -334,12 +422,17 @@ int pond_batch_size(const pond_batch *b, int *out)
 int pond_batch_destroy(pond_batch *b)
 {
     if (!b) return POND_OK;
-    if (b->stream) (void)hipStreamSynchronize(b->stream);
+    if (b->stream) (void)finish(b);
     for (pond_handle *h : b->members) h->batch = nullptr;
     drop_graphs(b);
     if (b->desc_d) (void)hipFree(b->desc_d);
     if (b->flags_d) (void)hipFree(b->flags_d);
     if (b->capture_stream) (void)hipStreamDestroy(b->capture_stream);
+    if (b->fork) (void)hipEventDestroy(b->fork);
+    for (hipEvent_t e : b->join)
+        if (e) (void)hipEventDestroy(e);
+    for (hipStream_t st : b->beside)
+        if (st) (void)hipStreamDestroy(st);
     if (b->own_stream && b->stream) (void)hipStreamDestroy(b->stream);
     delete b;
     return POND_OK;

@@ -3,6 +3,7 @@
 #include <cstdio>
 #include <memory>
 #include <new>
+#include <set>
 #include <string>
 
 #include "pond_handle.h"
@@ -57,8 +58,9 @@ static std::unique_ptr<pond_handle> member(int tile, bool fused)
     return h;
 }
 
-// a batch on device 0 of `groups` groups, stepped while `current` is the current device
-static void step(int groups, bool fused, int current)
+// a batch on device 0 of `groups` groups, stepped while `current` is the current device; its long
+// runs take `side_by_side` streams
+static void step(int groups, bool fused, int current, int side_by_side)
 {
     const int streams = fake::streams, events = fake::events;
     pond_batch *b = nullptr;
@@ -73,7 +75,11 @@ static void step(int groups, bool fused, int current)
     const int run = fused ? kFusedRun : 2 * kRunPairs;
     for (int change = 0; change < 3; ++change) {
         launches = elsewhere = 0;
+        fake::graph_launches.clear();
         CHECK(pond_batch_step(b, 2 * run) == POND_OK);
+        const std::set<hipStream_t> used(fake::graph_launches.begin(), fake::graph_launches.end());
+        CHECK((int)used.size() == side_by_side && (int)fake::graph_launches.size() == 2 * side_by_side);
+        for (hipStream_t st : used) CHECK(st->device == 0);
         CHECK(launches == run * groups * (fused ? 1 : 2) && elsewhere == 0);
         CHECK(fake::device == current && fake::captures == 0);
         CHECK(pond_batch_remove(b, h[0].get()) == POND_OK && pond_batch_add(b, h[0].get()) == POND_OK);
@@ -84,12 +90,26 @@ static void step(int groups, bool fused, int current)
     fake::device = 0;
 }
 
-// a batch's runs are captured for its own device, whichever is current
+// the streams of a batch are of its own device, whichever is current
 static void device()
 {
     for (int current : {0, 1})
         for (bool fused : {true, false})
-            for (int groups : {1, 2, 6}) step(groups, fused, current);
+            for (int groups : {1, 2, 3, 6}) step(groups, fused, current, groups < 3 ? groups : 3);
+}
+
+// with fewer streams or events than asked for, fewer groups run side by side
+static void shortage()
+{
+    for (int left : {0, 1, 2}) {
+        fake::streams_left = 2 + left; // (the batch's own two)
+        step(4, true, 0, 1 + left);
+    }
+    fake::streams_left = 1 << 30;
+    for (int left : {0, 1, 2, 3}) {
+        fake::events_left = left; // one to fork, one to join each stream
+        step(4, true, 0, left < 2 ? 1 : left);
+    }
 }
 
 // a capture allocates nothing of its own: an exception there would leave the C entry with the
@@ -97,13 +117,14 @@ static void device()
 static void memory()
 {
     memory_short = true;
-    for (bool fused : {true, false}) step(6, fused, 0);
+    for (bool fused : {true, false}) step(6, fused, 0, 3);
 }
 
 int main(int, char **argv)
 {
     const std::string what = argv[1];
     if (what == "device") device();
+    else if (what == "shortage") shortage();
     else if (what == "memory") memory();
     else return 255;
     return 0;

@@ -50,6 +50,7 @@ struct Copy {
 inline std::recursive_mutex lock;
 inline std::vector<Copy> copies;          // every hipMemcpyAsync
 inline std::map<const char *, size_t> pinned, on_device; // live hipHostMalloc and hipMalloc allocations
+inline std::vector<hipStream_t> graph_launches; // the stream of each
 inline int streams = 0, events = 0, captures = 0, events_left = 1 << 30, streams_left = 1 << 30;
 inline int device_of(hipStream_t s) { return (size_t)s <= 2 ? device : s->device; }
 inline bool within(const std::map<const char *, size_t> &blocks, const void *p)
@@ -169,4 +170,4 @@ inline hipError_t hipStreamEndCapture(hipStream_t s, hipGraph_t *g)
 inline hipError_t hipGraphDestroy(hipGraph_t g) { return std::free(g), hipSuccess; }
 inline hipError_t hipGraphInstantiate(hipGraphExec_t *x, hipGraph_t, void *, char *, size_t) { return *x = (ihipGraph *)std::malloc(1), hipSuccess; }
 inline hipError_t hipGraphExecDestroy(hipGraphExec_t x) { return std::free(x), hipSuccess; }
-inline hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) { return hipSuccess; }
+inline hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t s) { return fake::graph_launches.push_back(s), hipSuccess; }

@@ -40,6 +40,6 @@ def test_read_back_on_one_core(program):
     run(program("readback"), "one_core", preexec_fn=lambda: os.sched_setaffinity(0, sorted(os.sched_getaffinity(0))[:1]))
 
 
-@pytest.mark.parametrize("what", ["device", "memory"])
+@pytest.mark.parametrize("what", ["device", "shortage", "memory"])
 def test_batch(program, what):
     run(program("batch", "pond_batch.hip"), what)
