@@ -22,13 +22,13 @@ namespace pond {
 // to the caller's memory, faulting its pages side by side: 2048^2 (201 MB) 6.0 ms instead of
 // 20.9, 1024 x 512 (25 MB) 0.8 instead of 1.5, or 1.5 instead of 3.6 into pages new to the process.
 // Where all fields fit a piece the kernel that forms them writes them there (hipHostMalloc'ed
-// memory is the device's too): five copies of a 1000-node lattice took 134 us.  A copy into
-// the piece would be as fast, but the first one above 16 KiB starts a copy engine, 6 ms that
-// a process of such lattices does not pay otherwise.  Parts of more fields that fit a piece
-// take one copy.  Between the sizes the runtime's own copies stay:
-// there the gain is at most 0.3 ms, and helpers that meet another pool's spinning threads wait
-// milliseconds for a core (512^2 right after a conversion on all 16 cores: 0.8 ms by the
-// runtime, 1.2 with one helper, 2.1 with three, 3.8 with five).
+// memory is the device's too): 1000 nodes take 34 us, by five copies 134.  A copy into the
+// piece takes 41, but the first one above 16 KiB starts a copy engine, 6 ms that a process of
+// such lattices does not pay otherwise.  Parts of more fields that fit a piece take one copy.
+// Between the sizes the runtime's own copies stay: there the gain is at most 0.3 ms, and
+// helpers that meet another pool's spinning threads wait milliseconds for a core (512^2 right
+// after a conversion on all 16 cores: 0.8 ms by the runtime, 1.2 with one helper, 2.1 with
+// three, 3.8 with five).
 //
 // The pinned pieces are one allocation of at most kStageBytes for the process, made by the
 // first read-back, freed with the last handle.  A read-back that finds it in use (another

@@ -71,3 +71,19 @@ def test_read_backs_side_by_side():
     for lat in lats:
         lat.close()
     assert not bad
+
+
+@pytest.mark.parametrize("where", ["page-locked", "device"])
+@pytest.mark.parametrize("n", [(30, 30), (241, 183), (900, 701)])
+def test_arrays_in_other_memory(n, where):
+    """Page-locked arrays, and arrays on the device, hold the bits that pageable ones do."""
+    torch = pytest.importorskip("torch")
+    print(f"readback {n} into {where} memory", flush=True)
+    with lattice(*n, seed=4) as lat:
+        ref = read(lat, ("rho", "u", "T", "p", "E"))
+        kw = dict(pin_memory=True) if where == "page-locked" else dict(device="cuda")
+        out = {k: torch.full((v.size,), float("nan"), dtype=torch.float64, **kw) for k, v in ref.items()}
+        torch.cuda.synchronize()
+        dp = ctypes.POINTER(ctypes.c_double)
+        assert pond.load().pond_moments(lat._h, *(ctypes.cast(v.data_ptr(), dp) for v in out.values())) == pond.POND_OK
+        assert all(np.array_equal(v.cpu().numpy(), ref[k]) for k, v in out.items())
